@@ -22,6 +22,10 @@ constexpr int kLdsMaxN = 16384;
 constexpr int kMaxN = 65536;
 constexpr int kMaxSegRows = 1024;
 constexpr int kShortRowN = 2048;  // batches up to this n take the short-row row sweep
+// Instances up to this n (int16 W, Sinkhorn, fixed ladder) run in one workgroup
+// that holds them on chip (sk_small.hip), with a kernel per 64 columns.
+constexpr int kSmallN = 256;
+constexpr int kSmallClasses = kSmallN / kWave;
 constexpr int kFusedSlots = 256;  // workgroups (and column-partial slots) of the fused kernel
 constexpr int kMaxRowGrid = 1024;  // row-sweep workgroups (bounds table sized for it)
 constexpr int kRealTile = 256;     // columns per column tile of the real-weight sweeps
@@ -80,7 +84,7 @@ struct Inst {
     int32_t n_p;
     int32_t ladder[SK_MAX_LADDER];
     float tol;
-    int32_t pad1;
+    int32_t small;          // 1: iterated by k_small, not by the sweeps
     int64_t max_iters;
     int32_t *F[2];          // row potential, integer part (ping-pong by iteration parity)
     float *phi[2];          // row potential, fraction
@@ -111,7 +115,9 @@ struct Inst {
     uint32_t *rowres;
     // residual / drift slots the stored-K row sweep writes (one per workgroup)
     int32_t kres_slots;
-    int32_t pad3;
+    // lists kept in the descriptor array itself: entry b of the instances
+    // with `small` set (by class, the largest first) and of the others
+    int32_t small_idx;
     // the caller's W when W is the library's padded copy (n % 8 != 0),
     // else nullptr; copied once per batch before the input scan
     const int16_t *Wsrc;
@@ -123,7 +129,7 @@ struct Inst {
     // within a few p times the weight range.
     const float *Wr;
     float wref;
-    int32_t pad2;
+    int32_t sweep_idx;
     // p of the current stage is ctl->p * pscale: 1 for int16 W; with the
     // prescaling of Section 4.1.1, 1 / (w_max - w_min) when that exceeds 1
     double pscale;
@@ -255,8 +261,13 @@ hipError_t launch_nt_product(const Inst *d_insts, const RowUnit *d_rows, int nro
 hipError_t launch_nt_step(const Inst *d_insts, NtCtl *nt, NtVec vec, int n, hipStream_t st);
 hipError_t launch_nt_fold(const Inst *d_insts, const NtCtl *nt, NtVec vec, int n, int last,
                           hipStream_t st);
+// The instances insts[0 .. count).sweep_idx.
 hipError_t launch_iter_end(const Inst *d_insts, int count, hipStream_t st,
                            hipEvent_t stop = nullptr);
+// Up to `budget` iterations of the small instances; counts[c]: how many have
+// 64 c < n <= 64 (c + 1). The list of small_idx holds the largest class first.
+hipError_t launch_small(const Inst *d_insts, const int *counts, int budget, hipStream_t st);
+hipError_t set_small_attributes();
 enum : int { kFinOnePass = 1, kFinStoredK = 2 };
 hipError_t launch_col_finalize(const Inst *d_insts, const FinUnit *d_units, int nunits, int grid,
                                int mode, hipStream_t st);

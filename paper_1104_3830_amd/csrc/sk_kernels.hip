@@ -548,7 +548,7 @@ __global__ __launch_bounds__(kIterEndThreads) void k_iter_end(const Inst *__rest
     __shared__ int redi[kIterEndThreads];
     __shared__ float red[kIterEndThreads];
     __shared__ float tab[kTabN];
-    const Inst &I = insts[blockIdx.x];
+    const Inst &I = insts[insts[blockIdx.x].sweep_idx];
     Ctl *ctl = I.ctl;
     if (ctl->state != ST_RUNNING) return;
     const int n = I.n;

@@ -728,7 +728,7 @@ sk_status run_single_k(sk_ctx *ctx, Batch &B, const sk_params *prm, const StageH
             // finalise and end of iteration: short, not stamped
             KCHK(launch_col_finalize(B.d_insts, B.d_fins, (int)B.h_fins.size(), B.fin_grid,
                                      kFinStoredK | (I0.fused ? kFinOnePass : 0), ctx->stream));
-            KCHK(launch_iter_end(B.d_insts, B.count, ctx->stream));
+            KCHK(launch_iter_end(B.d_insts, B.nsweep, ctx->stream));
         }
         if (ctx->prof.on) {
             if ((st = read_ctl(ctx, B)) != SK_OK) return st;

@@ -29,8 +29,14 @@ inline size_t gq_lds_bytes(int32_t n) { return n > kLdsMaxN ? 0 : 8 * (size_t)pa
 struct Batch {
     int count = 0;
     int nmax = 0;
+    int nsweep = 0, nsmall = 0;     // instances iterated by the sweeps, and by k_small
+    int small_class[kSmallClasses] = {};  // of the latter, those with 64 c < n <= 64 (c + 1)
+    int sweep_nmax = 0;  // largest n of the former
     std::vector<Inst> h_insts;
+    // row units of every instance (input scan, FP64 check, CSR passes), those
+    // of the swept instances first; the other tables hold swept instances only
     std::vector<RowUnit> h_rows;
+    int nsweep_rows = 0;
     std::vector<ColUnit> h_cols;
     std::vector<FinUnit> h_fins;
     Inst *d_insts = nullptr;
@@ -77,7 +83,7 @@ enum KernelId {
     KID_ROW_K_DETECT, KID_COL_K_DETECT, KID_ROW_K_IDLE, KID_COL_K_IDLE,
     KID_FUSED, KID_FUSED_DETECT, KID_FUSED_IDLE,
     KID_NT_PRODUCT, KID_NT_STEP, KID_NT_PRODUCT_IDLE, KID_NT_STEP_IDLE,
-    KID_PAD_COPY,
+    KID_PAD_COPY, KID_SMALL,
     KID_COUNT
 };
 extern const char *kKernelNames[KID_COUNT];
@@ -187,6 +193,8 @@ sk_status read_ctl(sk_ctx *ctx, Batch &B);
 // chained: the previous launch on the stream is the end-of-iteration launch
 // of the previous call (timing then starts from that launch's end stamp).
 sk_status iterate_i16(sk_ctx *ctx, Batch &B, bool chained = false);
+// One launch of up to `budget` iterations of the batch's small instances.
+sk_status iterate_small(sk_ctx *ctx, Batch &B, int budget);
 // Iterates until no instance is running (done, error, or paused at a stage
 // end); first_stage: the stage the instances start this call in (launch tags).
 sk_status run_batch_i16(sk_ctx *ctx, Batch &B, const sk_params *prm, int first_stage = 0);

@@ -106,7 +106,7 @@ const char *kKernelNames[KID_COUNT] = {"init", "row_sweep", "col_sweep", "check_
                                        "col_sweep_k:detect", "row_sweep_k:idle",
                                        "col_sweep_k:idle", "fused", "fused:detect", "fused:idle",
                                        "nt_product", "nt_step", "nt_product:idle",
-                                       "nt_step:idle", "pad_copy"};
+                                       "nt_step:idle", "pad_copy", "small"};
 
 hipEvent_t Profiler::take() {
     if (!pool.empty()) {
@@ -257,6 +257,7 @@ sk_status sk_create(sk_ctx **out, int device, void *hip_stream, void *arena_dev_
         if (!g_attr_done) {
             if (set_kernel_attributes() != hipSuccess) return SK_EDEVICE;
             if (set_k_attributes() != hipSuccess) return SK_EDEVICE;
+            if (set_small_attributes() != hipSuccess) return SK_EDEVICE;
             if (set_real_attributes() != hipSuccess) return SK_EDEVICE;
             g_attr_done = true;
         }
@@ -388,6 +389,11 @@ bool sk::carve_instance(Bump &bump, const int16_t *W, int64_t pitch, int32_t nn,
     I.fused = prm->fused ? 1 : 0;
     I.deform_a = prm->deform_a > 0.0 ? prm->deform_a : 0.0;
     I.fused_grid = std::min(kFusedSlots, std::max(1, nn / 2));
+    // by size and options alone, so that a result does not depend on what
+    // else is in the batch (the deformed iteration moves p, and with it every
+    // entry, each time: it stays with the sweeps)
+    I.small = nn <= kSmallN && !Wr && prm->storage == SK_W_I16 && !prm->fused &&
+              prm->method == SK_SINKHORN && I.deform_a <= 0.0;
     for (int b = 0; b < 2; ++b) {
         I.F[b] = bump.take<int32_t>(nn);
         I.phi[b] = bump.take<float>(nn);
@@ -438,16 +444,37 @@ sk_status sk::finish_tables(sk_ctx *ctx, Bump &bump, Batch &B) {
     B.h_rows.clear();
     B.h_cols.clear();
     B.h_fins.clear();
-    B.nmax = 0;
+    B.nmax = B.sweep_nmax = 0;
+    B.nsweep = B.nsmall = 0;
+    for (int &c : B.small_class) c = 0;
     int64_t cpart = 0;
     for (int k = 0; k < B.count; ++k) {
         const Inst &I = B.h_insts[k];
         cpart = std::max<int64_t>(cpart, (int64_t)I.nseg * I.n);
+        B.nmax = std::max(B.nmax, I.n);
+        if (I.small) {
+            B.nsmall += 1;
+            B.small_class[(I.n - 1) / kWave] += 1;
+            continue;
+        }
         for (int r = 0; r < I.n; r += kRowWaves) B.h_rows.push_back(RowUnit{k, r});
         for (int s = 0; s < I.nseg; ++s)
             for (int tt = 0; tt < I.ntiles; ++tt) B.h_cols.push_back(ColUnit{k, tt, s, 0});
         for (int g = 0; g * kFinCols < I.n; ++g) B.h_fins.push_back(FinUnit{k, g});
-        B.nmax = std::max(B.nmax, I.n);
+        B.sweep_nmax = std::max(B.sweep_nmax, I.n);
+        B.h_insts[B.nsweep++].sweep_idx = k;
+    }
+    B.nsweep_rows = (int)B.h_rows.size();
+    int at[kSmallClasses];
+    for (int c = kSmallClasses - 1, first = 0; c >= 0; --c) {
+        at[c] = first;
+        first += B.small_class[c];
+    }
+    for (int k = 0; k < B.count; ++k) {
+        const Inst &I = B.h_insts[k];
+        if (!I.small) continue;
+        for (int r = 0; r < I.n; r += kRowWaves) B.h_rows.push_back(RowUnit{k, r});
+        B.h_insts[at[(I.n - 1) / kWave]++].small_idx = k;
     }
     B.d_insts = bump.take<Inst>(B.count);
     B.d_ctl_all = bump.take<Ctl>(B.count);
@@ -471,7 +498,7 @@ sk_status sk::finish_tables(sk_ctx *ctx, Bump &bump, Batch &B) {
     B.row_lds = lds;
     B.row_lds_k = sizeof(float) * (size_t)((B.nmax + 7) / 8 * 8);
     B.row_grid = (int)std::max<size_t>(
-        1, std::min<size_t>({B.h_rows.size(), (size_t)ctx->num_cus * per_cu, (size_t)kMaxRowGrid}));
+        1, std::min<size_t>({B.nsweep > 0 ? (size_t)B.nsweep_rows : B.h_rows.size(), (size_t)ctx->num_cus * per_cu, (size_t)kMaxRowGrid}));
     // one workgroup per CU: with two (and four loads in flight per lane) the
     // BF16 row sweep at n = 16384 ran 99 us instead of 89 us, more
     // concurrent row streams than HBM serves well
@@ -489,7 +516,7 @@ sk_status sk::finish_tables(sk_ctx *ctx, Bump &bump, Batch &B) {
     // Integer costs: equal units split exactly evenly.
     constexpr int64_t kCostCols = 512;
     {
-        const size_t nu = B.h_rows.size();
+        const size_t nu = (size_t)B.nsweep_rows;
         const int g = B.row_grid;
         std::vector<int64_t> cost(nu);
         int64_t total = 0;
@@ -533,10 +560,12 @@ sk_status sk::upload_batch(sk_ctx *ctx, Batch &B) {
     HIPCHK(ctx, hipMemcpyAsync(B.d_row_bounds, B.h_row_bounds.data(),
                                sizeof(int32_t) * B.h_row_bounds.size(), hipMemcpyHostToDevice,
                                ctx->stream));
-    HIPCHK(ctx, hipMemcpyAsync(B.d_cols, B.h_cols.data(), sizeof(ColUnit) * B.h_cols.size(),
-                               hipMemcpyHostToDevice, ctx->stream));
-    HIPCHK(ctx, hipMemcpyAsync(B.d_fins, B.h_fins.data(), sizeof(FinUnit) * B.h_fins.size(),
-                               hipMemcpyHostToDevice, ctx->stream));
+    if (B.nsweep > 0) {
+        HIPCHK(ctx, hipMemcpyAsync(B.d_cols, B.h_cols.data(), sizeof(ColUnit) * B.h_cols.size(),
+                                   hipMemcpyHostToDevice, ctx->stream));
+        HIPCHK(ctx, hipMemcpyAsync(B.d_fins, B.h_fins.data(), sizeof(FinUnit) * B.h_fins.size(),
+                                   hipMemcpyHostToDevice, ctx->stream));
+    }
     bool pads = false;
     for (const Inst &I : B.h_insts) pads |= I.Wsrc != nullptr;
     if (pads)
@@ -593,7 +622,7 @@ sk_status sk::iterate_i16(sk_ctx *ctx, Batch &B, bool chained) {
                                                       I.nt, ctx->stream)));
         HIPCHK(ctx, launch_col_finalize(B.d_insts, B.d_fins, (int)B.h_fins.size(), B.fin_grid,
                                         kFinOnePass, ctx->stream));
-        HIPCHK(ctx, launch_iter_end(B.d_insts, B.count, ctx->stream));
+        HIPCHK(ctx, launch_iter_end(B.d_insts, B.nsweep, ctx->stream));
         pf.iter_end_stamp = -1;
         return SK_OK;
     }
@@ -614,24 +643,35 @@ sk_status sk::iterate_i16(sk_ctx *ctx, Batch &B, bool chained) {
         HIPCHK(ctx, launch_row_sweep_real(B.d_insts, B.d_rows, (int)B.h_rows.size(), B.row_grid,
                                           B.row_lds, nt, I0.vec8, ctx->stream, e1));
     else
-        HIPCHK(ctx, launch_row_sweep(B.d_insts, B.d_rows, (int)B.h_rows.size(), B.d_row_bounds,
-                                     B.row_grid, B.row_lds, nt, B.nmax <= kShortRowN, gcol, ctx->stream, e1));
+        HIPCHK(ctx, launch_row_sweep(B.d_insts, B.d_rows, B.nsweep_rows, B.d_row_bounds, B.row_grid,
+                                     B.row_lds, nt, B.sweep_nmax <= kShortRowN, gcol, ctx->stream, e1));
     hipEvent_t e2 = pf.kernel_stamp(&s2);
     if (I0.Wr)
         HIPCHK(ctx, launch_col_sweep_real(B.d_insts, B.d_cols, (int)B.h_cols.size(), B.col_grid, nt,
                                           I0.vec8, ctx->stream, e2));
     else
         HIPCHK(ctx, launch_col_sweep(B.d_insts, B.d_cols, (int)B.h_cols.size(), B.col_grid, nt,
-                                     B.nmax <= kShortRowN, ctx->stream, e2));
+                                     B.sweep_nmax <= kShortRowN, ctx->stream, e2));
     pf.add(KID_ROW, s0, s1);
     pf.add(KID_COL, s1, s2);
     HIPCHK(ctx, launch_col_finalize(B.d_insts, B.d_fins, (int)B.h_fins.size(), B.fin_grid, 0,
                                     ctx->stream));
     hipEvent_t e3 = pf.kernel_stamp(&s3);
-    HIPCHK(ctx, launch_iter_end(B.d_insts, B.count, ctx->stream, e3));
+    HIPCHK(ctx, launch_iter_end(B.d_insts, B.nsweep, ctx->stream, e3));
     pf.iter_end_stamp = s3;
     return SK_OK;
 }
+
+sk_status sk::iterate_small(sk_ctx *ctx, Batch &B, int budget) {
+    if (B.nsmall == 0) return SK_OK;
+    HIPCHK(ctx, PROF(ctx, KID_SMALL, launch_small(B.d_insts, B.small_class, budget, ctx->stream)));
+    return SK_OK;
+}
+
+// Iterations per launch of the small instances: a launch of a few
+// milliseconds at most, so that a long ladder stays in the host's hands (a
+// read-back per launch, ~15 us).
+static constexpr int kSmallBudget = 2048;
 
 // Runs the ladder of every instance to completion (device-side stopping).
 // With timing on, launches are tagged afterwards: a triple (row, column,
@@ -649,23 +689,30 @@ sk_status sk::run_batch_i16(sk_ctx *ctx, Batch &B, const sk_params *prm, int fir
     // block of a paused stage is sized by the previous stage's iterations.
     constexpr int kTailBlock = 8;
     int blk = check;
+    bool swept = B.nsweep > 0;  // the sweeps have a running instance
     if (B.count == 1 && B.h_insts[0].pause && first_stage > 0)
         blk = (int)std::min<int64_t>(check, std::max<int64_t>(
                                                 4, ctx->h_ctl[0].stage_iters[first_stage - 1] + 2));
     for (;;) {
-        for (int k = 0; k < blk; ++k) {
-            sk_status s = iterate_i16(ctx, B, k > 0);
-            if (s != SK_OK) return s;
-        }
-        launched += blk;
-        sk_status s = read_ctl(ctx, B);
+        if (swept)
+            for (int k = 0; k < blk; ++k) {
+                sk_status s = iterate_i16(ctx, B, k > 0);
+                if (s != SK_OK) return s;
+            }
+        sk_status s = iterate_small(ctx, B, kSmallBudget);
         if (s != SK_OK) return s;
+        // every running instance has moved on by its block
+        launched += swept ? blk : kSmallBudget;
+        if ((s = read_ctl(ctx, B)) != SK_OK) return s;
         bool running = false, tail = true;
+        swept = false;
         for (int k = 0; k < B.count; ++k) {
             const Ctl &c = ctx->h_ctl[k];
             if (c.state != ST_RUNNING) continue;
             running = true;
             const Inst &I = B.h_insts[k];
+            if (I.small) continue;
+            swept = true;
             // (the deformed iteration is one long stage: full blocks)
             const bool last = I.deform_a <= 0.0 && c.stage + 1 >= I.n_p;
             tail &= last || I.pause;
@@ -680,6 +727,7 @@ sk_status sk::run_batch_i16(sk_ctx *ctx, Batch &B, const sk_params *prm, int fir
         std::vector<int64_t> detect;
         int64_t working = 0;
         for (int k = 0; k < B.count; ++k) {
+            if (B.h_insts[k].small) continue;
             const Ctl &c = ctx->h_ctl[k];
             int64_t t = 0;
             for (int s = first_stage; s <= std::min(c.stage, prm->n_p - 1); ++s) {

@@ -106,6 +106,10 @@ static void release_staging(Server *S, Request *r) {
     r->staging = nullptr;
 }
 
+// Iterations per tick of the small instances (about as long as a tick of the
+// sweeps' iterations).
+static const int kServeSmallIters = 256;
+
 static const size_t kTablesBytes = size_t(64) << 20;
 
 // Host copy of a submitted W into staging: one thread per kCopyChunk bytes,
@@ -437,7 +441,8 @@ static void serve_loop(Server *S) {
             dirty = false;
         }
         for (int it = 0; it < S->iters_per_tick && st == SK_OK && e == hipSuccess; ++it)
-            st = iterate_i16(ctx, S->B);
+            if (S->B.nsweep > 0) st = iterate_i16(ctx, S->B);
+        if (st == SK_OK && e == hipSuccess) st = iterate_small(ctx, S->B, kServeSmallIters);
         if (st == SK_OK && e == hipSuccess) st = read_ctl(ctx, S->B);
         if (st != SK_OK || e != hipSuccess) {
             std::lock_guard<std::mutex> g(S->mu);
