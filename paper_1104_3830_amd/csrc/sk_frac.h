@@ -38,6 +38,13 @@ __device__ __forceinline__ void exp_frac(float xf, double &r) {
     r = fma(q, x, 1.0);
 }
 
+// k + f with |f| <= 1/2 (k and f as they are where |f| <= 1/2 already).
+__device__ __forceinline__ void unit_frac(int &k, float &f) {
+    const float r = rintf(f);
+    k += (int)r;
+    f -= r;
+}
+
 // -log(S) = k + f with k an integer and |f| <= 1/2, for S in [2^-64, 2^64].
 // S = 2^e m, m in [1/sqrt 2, sqrt 2); with y = m - 1 (exact) and
 // s = y / (2 + y), log m = 2 atanh(s) = y - s y + s^3 (2/3 + 2/5 s^2 + ...).

@@ -26,6 +26,16 @@ constexpr int kShortRowN = 2048;  // batches up to this n take the short-row row
 // that holds them on chip (sk_small.hip), with a kernel per 64 columns.
 constexpr int kSmallN = 256;
 constexpr int kSmallClasses = kSmallN / kWave;
+// Above it and up to this n, one launch per iteration (sk_mid.hip), a
+// workgroup per kMidRows rows.
+constexpr int kMidN = 1024;
+constexpr int kMidRows = 32;
+constexpr int kMidMaxBlocks = kMidN / kMidRows;
+// Up to this many blocks (one workgroup per compute unit) each takes the whole
+// column step itself; above, a launch of its own takes it once per instance,
+// and a workgroup sweeps runs of up to kMidRun blocks.
+constexpr int kMidFoldUnits = 256;
+constexpr int kMidRun = 8;
 constexpr int kFusedSlots = 256;  // workgroups (and column-partial slots) of the fused kernel
 constexpr int kMaxRowGrid = 1024;  // row-sweep workgroups (bounds table sized for it)
 constexpr int kRealTile = 256;     // columns per column tile of the real-weight sweeps
@@ -62,6 +72,7 @@ struct Ctl {
     float last_res;         // residual of the last measured iterate
     uint32_t need_absorb;   // stored K: K must be recomputed before the next K sweep
     uint32_t drift_bits;    // stored K: max |log2 a_i|, |log2 b_j| since the last absorb (float bits)
+    uint32_t pending;       // k_mid: the last launch left the sums of an iteration
     int64_t stage_iters[SK_MAX_LADDER];
     // deformed iteration on real-valued weights: p of the current iteration
     // unrounded (p is its rounding, used by the integer path)
@@ -84,7 +95,8 @@ struct Inst {
     int32_t n_p;
     int32_t ladder[SK_MAX_LADDER];
     float tol;
-    int32_t small;          // 1: iterated by k_small, not by the sweeps
+    int16_t small;          // 1: iterated by k_small, not by the sweeps
+    int16_t mid;            // 1: iterated by k_mid, not by the sweeps
     int64_t max_iters;
     int32_t *F[2];          // row potential, integer part (ping-pong by iteration parity)
     float *phi[2];          // row potential, fraction
@@ -138,7 +150,29 @@ struct Inst {
     // sweep: (4 G_j, exp(gam_j)); FP64 check and CSR passes: (G_j, gam_j));
     // nullptr otherwise
     void *colpack;
+    // k_mid: the second copies of the controller and the column potentials
+    // (the row potentials have F[2], phi[2]; colpart holds two sets of slots)
+    Ctl *ctl2;
+    int32_t *G2;
+    float *gam2;
+    int32_t mid_idx;        // list of the instances with `mid` set
+    int32_t ord_idx;        // list of all instances in the order of their units
+    // FP64 check: scratch (see check_rsum and what follows it) and the row
+    // segments of its column pass
+    int32_t chk_seg, chk_nseg;
+    double *chk;
+    void *pot;              // the caller's potentials buffer (batches)
 };
+// Doubles of one of the check's arrays of n, and of the whole scratch.
+__host__ __device__ constexpr size_t check_stride(int n) { return ((size_t)n + 31) / 32 * 32; }
+__host__ __device__ constexpr size_t check_doubles(int n, int nseg) {
+    return 3 * check_stride(n) + ((size_t)nseg * n + 31) / 32 * 32;
+}
+// Row segments of the check's column pass: short ones up to this n, where the
+// sweep's segments would leave a handful of workgroups (n = 1003: 39 us on 8
+// of them).
+constexpr int kCheckShortN = 2048;
+constexpr int kCheckShortSeg = 32;
 constexpr int kRowResSlots = 64;    // = kWave: one wave reduces them
 constexpr int kRowResStride = 32;   // one 128-byte line per slot
 
@@ -268,21 +302,33 @@ hipError_t launch_iter_end(const Inst *d_insts, int count, hipStream_t st,
 // 64 c < n <= 64 (c + 1). The list of small_idx holds the largest class first.
 hipError_t launch_small(const Inst *d_insts, const int *counts, int budget, hipStream_t st);
 hipError_t set_small_attributes();
+// Two iterations of the instances insts[0 .. ninst).mid_idx over their units of
+// kMidRows rows (row0: the first row, and the count of blocks in the upper
+// half): first those of the instances with n > 512, then the others'. fold:
+// one block per unit, the column step in the same launch. d_units null: one
+// instance (index 0), its blocks in order.
+hipError_t launch_mid_pair(const Inst *d_insts, const RowUnit *d_units, int nwide, int nnarrow, int ninst, int fold,
+                           hipStream_t st);
 enum : int { kFinOnePass = 1, kFinStoredK = 2 };
 hipError_t launch_col_finalize(const Inst *d_insts, const FinUnit *d_units, int nunits, int grid,
                                int mode, hipStream_t st);
-hipError_t launch_check_rows(const Inst *d_insts, const RowUnit *d_units, int nunits, int grid,
-                             double *rsum, double *rmax, double logt, int64_t *counts,
-                             int32_t *hint, size_t lds_bytes, int nt_loads, int gcol, hipStream_t st);
-hipError_t launch_check_cols(const Inst *d_insts, int inst, int n, int nseg, int vec8,
-                             double *part, double *csum, int nt_loads, hipStream_t st);
+// The FP64 check. Tables of units, or for one instance (null) its index and
+// the number of its units; ended: only instances that are not running.
+hipError_t launch_check_rows(const Inst *d_insts, const RowUnit *d_units, int nunits, int grid, int ended,
+                             double logt, int64_t *counts, int32_t *hint, size_t lds_bytes, int nt_loads, int gcol,
+                             hipStream_t st);
+hipError_t launch_check_cols(const Inst *d_insts, const ColUnit *d_units, int inst, int nunits, int ended,
+                             int nt_loads, hipStream_t st);
+// first, ninst: the instances in the list ord_idx; out: four numbers per instance index.
+hipError_t launch_check_sums(const Inst *d_insts, const FinUnit *d_units, int inst, int nunits, int first, int ninst,
+                             int ended, double *out, hipStream_t st);
+hipError_t launch_copy_pot(const Inst *d_insts, const FinUnit *d_units, int inst, int nunits, void *pot, int in,
+                           hipStream_t st);
 hipError_t launch_prune_count(const Inst *d_insts, const RowUnit *d_units, int nunits, int grid,
                               double logt, int64_t *counts, size_t lds_bytes, int nt_loads, int gcol,
                               hipStream_t st);
 hipError_t launch_scan(const int64_t *counts, int64_t *row_ptr, int n, hipStream_t st,
                        int64_t *total_out = nullptr);
-hipError_t launch_check_reduce(const Inst *d_insts, int inst, const double *rsum,
-                               const double *rmax, const double *csum, double *out, hipStream_t st);
 hipError_t launch_prune_fill(const Inst *d_insts, const RowUnit *d_units, int nunits, int grid,
                              double logt, const int64_t *row_ptr, int32_t *col, int16_t *w,
                              size_t lds_bytes, int nt_loads, int gcol, hipStream_t st);
@@ -314,7 +360,7 @@ hipError_t launch_col_sweep_real(const Inst *d_insts, const ColUnit *d_units, in
                                  int nt_loads, int vec4, hipStream_t st, hipEvent_t stop = nullptr);
 hipError_t launch_check_real(const Inst *d_insts, const RowUnit *d_units, int nunits, int grid, int inst,
                              int n, int nseg, double *rsum, double *rmax, double logt, int64_t *counts,
-                             int32_t *hint, double *part, double *csum, hipStream_t st);
+                             int32_t *hint, double *part, hipStream_t st);
 hipError_t launch_prune_fill_real(const Inst *d_insts, const RowUnit *d_units, int nunits, int grid,
                                   double logt, const int64_t *row_ptr, int32_t *col, float *w, int n,
                                   hipStream_t st);

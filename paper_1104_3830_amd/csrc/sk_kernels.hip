@@ -664,6 +664,13 @@ __device__ __forceinline__ int kept_skip(double logt) {
     return (int)fmax(fmin(floor(logt), 1073741824.0), -1073741824.0) - 2;
 }
 
+// Parts of an instance's scratch: row sums, row maxima, per unit of 64 the
+// four reduced numbers, column partials [chk_nseg][n].
+__device__ __forceinline__ double *check_rsum(const Inst &I) { return I.chk; }
+__device__ __forceinline__ double *check_rmax(const Inst &I) { return I.chk + check_stride(I.n); }
+__device__ __forceinline__ double *check_part4(const Inst &I) { return I.chk + 2 * check_stride(I.n); }
+__device__ __forceinline__ double *check_cpart(const Inst &I) { return I.chk + 3 * check_stride(I.n); }
+
 // Stages the column potentials (G_j, bits of gam_j) for the instance in LDS;
 // swizzled like the row sweep when 8-wide chunks are used. log v_j in FP64 is
 // (double)G_j + (double)gam_j.
@@ -901,11 +908,12 @@ __device__ __forceinline__ void check_row_v8(const Inst &I, GQ gq, int2 *qe, int
 
 // GCOL: one instance with n > kLdsMaxN, its column entries read from
 // I.colpack (packed by k_col_pack, mode 1) instead of staged in LDS.
+// ended: instances still running are passed over (so in the other kernels of
+// the check).
 template <bool NT, bool GCOL>
 __global__ __launch_bounds__(kRowWaves * kWave) void k_check_rows(const Inst *__restrict__ insts,
                                                                     const RowUnit *__restrict__ units,
-                                                                    int nunits, double *rsum,
-                                                                    double *rmax, double logt,
+                                                                    int nunits, int ended, double logt,
                                                                     int64_t *counts, int32_t *hint) {
     extern __shared__ int2 gq_lds[];
     __shared__ int2 queue[kRowWaves][kWave];
@@ -926,6 +934,7 @@ __global__ __launch_bounds__(kRowWaves * kWave) void k_check_rows(const Inst *__
             // the queue and the results are the same.
             __shared__ int gG[kGTile];
             const Inst &I = insts[0];
+            double *rsum = check_rsum(I), *rmax = check_rmax(I);
             const int n = I.n, ntile = (n + kGTile - 1) / kGTile;
             // the row's state is wave-uniform: kept in scalar registers
             const bool sent = __builtin_amdgcn_readfirstlane(I.ctl->sent) != 0u;
@@ -970,6 +979,8 @@ __global__ __launch_bounds__(kRowWaves * kWave) void k_check_rows(const Inst *__
     for (int u = u0; u < u1; ++u) {
         const RowUnit un = units[u];
         const Inst &I = insts[un.inst];
+        if (ended && __builtin_amdgcn_readfirstlane(I.ctl->state) == ST_RUNNING) continue;
+        double *rsum = check_rsum(I), *rmax = check_rmax(I);
         if (un.inst != cur) {
             if (!GCOL) {
                 __syncthreads();
@@ -1049,40 +1060,36 @@ __global__ __launch_bounds__(kRowWaves * kWave) void k_check_rows(const Inst *__
     }
 }
 
-// Column sums in FP64, two passes: workgroup (256-column tile, row segment)
-// with one thread per column writes a partial to slot [segment][column]
-// (coalesced along each row); then one thread per column adds its slots in
-// segment order.
-__global__ __launch_bounds__(256) void k_check_cols_part(const Inst *__restrict__ insts, int inst,
-                                                         double *part) {
-    const Inst &I = insts[inst];
-    const int n = I.n;
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    const int seg = blockIdx.y;
-    if (j >= n) return;
-    const int r0 = seg * I.seg_rows, r1 = min(n, r0 + I.seg_rows);
-    const int par = I.ctl->iter & 1;
-    const double p = (double)I.ctl->p;
-    const double g = (double)I.G[j] + (double)I.gam[j];
-    double s = 0.0;
-    for (int r = r0; r < r1; ++r) {
-        const int w = I.W[(int64_t)r * I.pitch + j];
-        if (w == SK_SENTINEL) continue;
-        const double lx = p * (double)w + g + ((double)I.F[par][r] + (double)I.phi[par][r]);
-        if (lx > kNegligibleLog) s += exp(lx);
-    }
-    part[(int64_t)seg * n + j] = s;
+// Column sums in FP64, two passes: a workgroup takes a (512-column tile, row
+// segment of chk_seg rows) and writes each column's partial to slot
+// [segment][column] of the instance's scratch (coalesced along each row); then
+// k_check_sum adds a column's slots.
+//
+// The unit of workgroup b: units[b], or for one instance (units null) its
+// tiles and segments in order.
+__device__ __forceinline__ ColUnit check_col_unit(const Inst *insts, const ColUnit *units, int inst) {
+    if (units) return units[blockIdx.x];
+    const int nt = (insts[inst].n + kColTile8 - 1) / kColTile8;
+    return ColUnit{inst, (int)blockIdx.x % nt, (int)blockIdx.x / nt, 0};
 }
 
-__global__ __launch_bounds__(256) void k_check_cols_sum(const Inst *__restrict__ insts, int inst,
-                                                        const double *part, double *csum) {
-    const Inst &I = insts[inst];
+// Rows without the 8-wide layout: one thread per column, twice.
+__device__ __forceinline__ void check_cols_v1(const Inst &I, const ColUnit un) {
     const int n = I.n;
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= n) return;
-    double s = 0.0;
-    for (int seg = 0; seg < I.nseg; ++seg) s += part[(int64_t)seg * n + j];
-    csum[j] = s;
+    const int r0 = un.seg * I.chk_seg, r1 = min(n, r0 + I.chk_seg);
+    const int par = I.ctl->iter & 1;
+    const double p = (double)I.ctl->p;
+    for (int j = un.tile * kColTile8 + (int)threadIdx.x; j < min(n, (un.tile + 1) * kColTile8); j += blockDim.x) {
+        const double g = (double)I.G[j] + (double)I.gam[j];
+        double s = 0.0;
+        for (int r = r0; r < r1; ++r) {
+            const int w = I.W[(int64_t)r * I.pitch + j];
+            if (w == SK_SENTINEL) continue;
+            const double lx = p * (double)w + g + ((double)I.F[par][r] + (double)I.phi[par][r]);
+            if (lx > kNegligibleLog) s += exp(lx);
+        }
+        check_cpart(I)[(int64_t)un.seg * n + j] = s;
+    }
 }
 
 // The same slots from 8 columns per lane (16-byte loads along each row) with
@@ -1114,16 +1121,23 @@ __device__ __forceinline__ void check_cols_add8(const int (&w)[8], int p, int2 r
 }
 
 template <bool NT>
-__global__ __launch_bounds__(kColWaves * kWave) void k_check_cols_part8(const Inst *__restrict__ insts,
-                                                                        int inst, double *part) {
+__global__ __launch_bounds__(kColWaves * kWave) void k_check_cols(const Inst *__restrict__ insts,
+                                                                  const ColUnit *__restrict__ units, int inst,
+                                                                  int ended) {
     __shared__ double red[kColWaves][kColTile8];
     __shared__ int2 rowf[kMaxSegRows];
-    const Inst &I = insts[inst];
+    const ColUnit un = check_col_unit(insts, units, inst);
+    const Inst &I = insts[un.inst];
+    if (ended && __builtin_amdgcn_readfirstlane(I.ctl->state) == ST_RUNNING) return;
+    if (!I.vec8) {
+        check_cols_v1(I, un);
+        return;
+    }
     const int n = I.n;
     const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-    const int ctile0 = blockIdx.x * kColTile8;
-    const int seg = blockIdx.y;
-    const int r0 = seg * I.seg_rows, r1 = min(n, r0 + I.seg_rows);
+    const int ctile0 = un.tile * kColTile8;
+    const int seg = un.seg;
+    const int r0 = seg * I.chk_seg, r1 = min(n, r0 + I.chk_seg);
     const int par = I.ctl->iter & 1;
     const int p = I.ctl->p;
     for (int r = r0 + (int)threadIdx.x; r < r1; r += blockDim.x)
@@ -1164,7 +1178,7 @@ __global__ __launch_bounds__(kColWaves * kWave) void k_check_cols_part8(const In
 #pragma unroll
     for (int c = 0; c < 8; ++c) red[wave][lane * 8 + c] = s[c];
     __syncthreads();
-    double *dst = part + (int64_t)seg * n + ctile0;
+    double *dst = check_cpart(I) + (int64_t)seg * n + ctile0;
     const int ncols = min(kColTile8, n - ctile0);
     for (int c = threadIdx.x; c < ncols; c += blockDim.x) {
         double t = red[0][c];
@@ -1174,40 +1188,101 @@ __global__ __launch_bounds__(kColWaves * kWave) void k_check_cols_part8(const In
     }
 }
 
-// Reduces the FP64 check of one instance to four numbers, in a fixed order:
-// out[0] = max_i |r_i - 1|, out[1] = max_j |c_j - 1|, out[2] = sum_i m_i,
-// out[3] = sum_j log v_j (the certificate is (out[2] - out[3]) / p).
-__global__ __launch_bounds__(256) void k_check_reduce(const Inst *__restrict__ insts, int inst,
-                                                      const double *rsum, const double *rmax,
-                                                      const double *csum, double *out) {
-    __shared__ double a[256], b[256], c[256], d[256];
-    const Inst &I = insts[inst];
-    const int n = I.n, t = threadIdx.x;
-    double ra = 0.0, ca = 0.0, sm = 0.0, sg = 0.0;
-    for (int i = t; i < n; i += 256) {
-        ra = fmax(ra, fabs(rsum[i] - 1.0));
-        ca = fmax(ca, fabs(csum[i] - 1.0));
-        sm += rmax[i];
-        sg += (double)I.G[i] + (double)I.gam[i];
-    }
-    a[t] = ra;
-    b[t] = ca;
-    c[t] = sm;
-    d[t] = sg;
+// The check of one unit of 64 rows and columns: each column's slots (four
+// threads per column, every fourth slot each), then the unit's max |r_i - 1|,
+// max |c_j - 1|, sum of the row maxima m_i and of log v_j. (One workgroup per
+// instance adding all columns' slots took 38 us at n = 8192, 10 at 16384.)
+__global__ __launch_bounds__(256) void k_check_sum(const Inst *__restrict__ insts, const FinUnit *__restrict__ units,
+                                                   int inst, int ended) {
+    __shared__ double part[4][kFinCols];
+    FinUnit un{inst, (int)blockIdx.x};
+    if (units) un = units[blockIdx.x];
+    const Inst &I = insts[un.inst];
+    if (ended && __builtin_amdgcn_readfirstlane(I.ctl->state) == ST_RUNNING) return;
+    const int n = I.n, ns = I.chk_nseg;
+    const int c = threadIdx.x % kFinCols, g = threadIdx.x / kFinCols;
+    const int j = un.group * kFinCols + c;
+    const double *q = check_cpart(I) + j;
+    double s = 0.0;
+    if (j < n)
+        for (int k = g; k < ns; k += 4) s += q[(int64_t)k * n];
+    part[g][c] = s;
     __syncthreads();
-    if (t == 0) {
-        double A = 0.0, Bm = 0.0, C = 0.0, D = 0.0;
-        for (int k = 0; k < 256; ++k) {
-            A = fmax(A, a[k]);
-            Bm = fmax(Bm, b[k]);
-            C += c[k];
-            D += d[k];
-        }
-        out[0] = A;
-        out[1] = Bm;
-        out[2] = C;
-        out[3] = D;
+    if (g > 0) return;
+    double ra = 0.0, ca = 0.0, sm = 0.0, sg = 0.0;
+    if (j < n) {
+        ca = fabs((part[0][c] + part[1][c]) + (part[2][c] + part[3][c]) - 1.0);
+        ra = fabs(check_rsum(I)[j] - 1.0);
+        sm = check_rmax(I)[j];
+        sg = (double)I.G[j] + (double)I.gam[j];
     }
+    ra = wave_max_d(ra);
+    ca = wave_max_d(ca);
+    sm = wave_sum_d(sm);
+    sg = wave_sum_d(sg);
+    if (c == 0) {
+        double *o = check_part4(I) + 4 * un.group;
+        o[0] = ra;
+        o[1] = ca;
+        o[2] = sm;
+        o[3] = sg;
+    }
+}
+
+// The units' numbers of one instance in a fixed order: out[4 k] =
+// max_i |r_i - 1|, max_j |c_j - 1|, sum_i m_i, sum_j log v_j (the certificate
+// is (out[2] - out[3]) / p). Workgroup b: instance `first` + b of the list
+// ord_idx.
+__global__ __launch_bounds__(kWave) void k_check_reduce(const Inst *__restrict__ insts, int first, int ended,
+                                                        double *out) {
+    const int k = insts[first + blockIdx.x].ord_idx;
+    const Inst &I = insts[k];
+    if (ended && __builtin_amdgcn_readfirstlane(I.ctl->state) == ST_RUNNING) return;
+    const int nu = (I.n + kFinCols - 1) / kFinCols;
+    const double *q = check_part4(I);
+    double ra = 0.0, ca = 0.0, sm = 0.0, sg = 0.0;
+    for (int u = threadIdx.x; u < nu; u += kWave) {
+        ra = fmax(ra, q[4 * u]);
+        ca = fmax(ca, q[4 * u + 1]);
+        sm += q[4 * u + 2];
+        sg += q[4 * u + 3];
+    }
+    ra = wave_max_d(ra);
+    ca = wave_max_d(ca);
+    sm = wave_sum_d(sm);
+    sg = wave_sum_d(sg);
+    if (threadIdx.x == 0) {
+        out[4 * k] = ra;
+        out[4 * k + 1] = ca;
+        out[4 * k + 2] = sm;
+        out[4 * k + 3] = sg;
+    }
+}
+
+// ---------------------------------------------------------------- potentials in and out
+// Between the caller's buffers (I.pot, or `pot` for one instance: F, phi, G,
+// gam, n each) and the instance's: the start of a warm run into parity 0, or
+// the committed potentials out. A unit is 64 indices of the four arrays. (As
+// copies they were four per instance, 2048 of 1.5 us for a batch of 512.)
+template <class T>
+__device__ __forceinline__ void copy_word(T *mine, char *theirs, int in) {
+    if (in) __builtin_memcpy(mine, theirs, 4);
+    else __builtin_memcpy(theirs, mine, 4);
+}
+__global__ __launch_bounds__(kFinCols) void k_copy_pot(const Inst *__restrict__ insts,
+                                                      const FinUnit *__restrict__ units, int inst, char *pot, int in) {
+    FinUnit un{inst, (int)blockIdx.x};
+    if (units) un = units[blockIdx.x];
+    const Inst &I = insts[un.inst];
+    const int n = I.n, i = un.group * kFinCols + (int)threadIdx.x;
+    if (i >= n) return;
+    const int par = in ? 0 : I.ctl->iter & 1;
+    char *theirs = (pot ? pot : (char *)I.pot) + 4 * (size_t)i;
+    const size_t next = 4 * (size_t)n;
+    copy_word(I.F[par] + i, theirs, in);
+    copy_word(I.phi[par] + i, theirs + next, in);
+    copy_word(I.G + i, theirs + 2 * next, in);
+    copy_word(I.gam + i, theirs + 3 * next, in);
 }
 
 // ---------------------------------------------------------------- prune
@@ -2110,43 +2185,44 @@ hipError_t launch_iter_end(const Inst *d_insts, int count, hipStream_t st, hipEv
     launch_stamped(k_iter_end, dim3(count), dim3(kIterEndThreads), 0, st, stop, d_insts);
     return hipGetLastError();
 }
-hipError_t launch_check_rows(const Inst *d_insts, const RowUnit *d_units, int nunits, int grid,
-                             double *rsum, double *rmax, double logt, int64_t *counts,
-                             int32_t *hint, size_t lds_bytes, int nt_loads, int gcol, hipStream_t st) {
+hipError_t launch_check_rows(const Inst *d_insts, const RowUnit *d_units, int nunits, int grid, int ended,
+                             double logt, int64_t *counts, int32_t *hint, size_t lds_bytes, int nt_loads, int gcol,
+                             hipStream_t st) {
     const dim3 g(grid), b(kRowWaves * kWave);
     if (gcol)
-        hipLaunchKernelGGL((k_check_rows<true, true>), g, b, 0, st, d_insts, d_units, nunits, rsum, rmax, logt,
-                           counts, hint);
+        hipLaunchKernelGGL((k_check_rows<true, true>), g, b, 0, st, d_insts, d_units, nunits, ended, logt, counts,
+                           hint);
     else if (nt_loads)
-        hipLaunchKernelGGL((k_check_rows<true, false>), g, b, lds_bytes, st, d_insts, d_units, nunits, rsum,
-                           rmax, logt, counts, hint);
+        hipLaunchKernelGGL((k_check_rows<true, false>), g, b, lds_bytes, st, d_insts, d_units, nunits, ended, logt,
+                           counts, hint);
     else
-        hipLaunchKernelGGL((k_check_rows<false, false>), g, b, lds_bytes, st, d_insts, d_units, nunits, rsum,
-                           rmax, logt, counts, hint);
+        hipLaunchKernelGGL((k_check_rows<false, false>), g, b, lds_bytes, st, d_insts, d_units, nunits, ended, logt,
+                           counts, hint);
     return hipGetLastError();
 }
 hipError_t launch_col_pack(const Inst *d_insts, int inst, int n, int mode, hipStream_t st) {
     hipLaunchKernelGGL(k_col_pack, dim3((pad8(n) + 255) / 256), dim3(256), 0, st, d_insts, inst, mode);
     return hipGetLastError();
 }
-hipError_t launch_check_reduce(const Inst *d_insts, int inst, const double *rsum,
-                               const double *rmax, const double *csum, double *out, hipStream_t st) {
-    hipLaunchKernelGGL(k_check_reduce, dim3(1), dim3(256), 0, st, d_insts, inst, rsum, rmax, csum, out);
+hipError_t launch_check_cols(const Inst *d_insts, const ColUnit *d_units, int inst, int nunits, int ended,
+                             int nt_loads, hipStream_t st) {
+    if (nt_loads)
+        hipLaunchKernelGGL(k_check_cols<true>, dim3(nunits), dim3(kColWaves * kWave), 0, st, d_insts, d_units, inst,
+                           ended);
+    else
+        hipLaunchKernelGGL(k_check_cols<false>, dim3(nunits), dim3(kColWaves * kWave), 0, st, d_insts, d_units, inst,
+                           ended);
     return hipGetLastError();
 }
-hipError_t launch_check_cols(const Inst *d_insts, int inst, int n, int nseg, int vec8,
-                             double *part, double *csum, int nt_loads, hipStream_t st) {
-    if (vec8 && nt_loads)
-        hipLaunchKernelGGL(k_check_cols_part8<true>, dim3((n + kColTile8 - 1) / kColTile8, nseg),
-                           dim3(kColWaves * kWave), 0, st, d_insts, inst, part);
-    else if (vec8)
-        hipLaunchKernelGGL(k_check_cols_part8<false>, dim3((n + kColTile8 - 1) / kColTile8, nseg),
-                           dim3(kColWaves * kWave), 0, st, d_insts, inst, part);
-    else
-        hipLaunchKernelGGL(k_check_cols_part, dim3((n + 255) / 256, nseg), dim3(256), 0, st, d_insts,
-                           inst, part);
-    hipLaunchKernelGGL(k_check_cols_sum, dim3((n + 255) / 256), dim3(256), 0, st, d_insts, inst,
-                       part, csum);
+hipError_t launch_check_sums(const Inst *d_insts, const FinUnit *d_units, int inst, int nunits, int first, int ninst,
+                             int ended, double *out, hipStream_t st) {
+    hipLaunchKernelGGL(k_check_sum, dim3(nunits), dim3(256), 0, st, d_insts, d_units, inst, ended);
+    hipLaunchKernelGGL(k_check_reduce, dim3(ninst), dim3(kWave), 0, st, d_insts, first, ended, out);
+    return hipGetLastError();
+}
+hipError_t launch_copy_pot(const Inst *d_insts, const FinUnit *d_units, int inst, int nunits, void *pot, int in,
+                           hipStream_t st) {
+    hipLaunchKernelGGL(k_copy_pot, dim3(nunits), dim3(kFinCols), 0, st, d_insts, d_units, inst, (char *)pot, in);
     return hipGetLastError();
 }
 hipError_t launch_prune_count(const Inst *d_insts, const RowUnit *d_units, int nunits, int grid,

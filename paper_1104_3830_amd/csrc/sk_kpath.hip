@@ -653,12 +653,13 @@ sk_status run_single_k(sk_ctx *ctx, Batch &B, const sk_params *prm, const StageH
                 const int n = I.n;
                 ctx->prof.begin(ctx->stream, KID_CHECK_ROWS);
                 KCHK(launch_check_k(B.d_insts, B.d_rows, (int)B.h_rows.size(), B.row_grid, 0, n,
-                                    I.nseg, storage, I.nt, B.d_rsum, B.d_cpart, B.d_csum, ctx->stream));
+                                    I.nseg, storage, I.nt, I.chk, I.chk + 3 * check_stride(n),
+                                    I.chk + check_stride(n), ctx->stream));
                 ctx->prof.end(ctx->stream);
                 std::vector<double> r(n), cs(n);
-                KCHK(hipMemcpyAsync(r.data(), B.d_rsum, 8 * (size_t)n, hipMemcpyDeviceToHost,
+                KCHK(hipMemcpyAsync(r.data(), I.chk, 8 * (size_t)n, hipMemcpyDeviceToHost,
                                     ctx->stream));
-                KCHK(hipMemcpyAsync(cs.data(), B.d_csum, 8 * (size_t)n, hipMemcpyDeviceToHost,
+                KCHK(hipMemcpyAsync(cs.data(), I.chk + check_stride(n), 8 * (size_t)n, hipMemcpyDeviceToHost,
                                     ctx->stream));
                 KCHK(hipStreamSynchronize(ctx->stream));
                 double rr = 0, cr = 0;
@@ -726,7 +727,7 @@ sk_status run_single_k(sk_ctx *ctx, Batch &B, const sk_params *prm, const StageH
                 pf.add(KID_COL_K, s1, s2);
             }
             // finalise and end of iteration: short, not stamped
-            KCHK(launch_col_finalize(B.d_insts, B.d_fins, (int)B.h_fins.size(), B.fin_grid,
+            KCHK(launch_col_finalize(B.d_insts, B.d_fins, B.nsweep_fins, B.fin_grid,
                                      kFinStoredK | (I0.fused ? kFinOnePass : 0), ctx->stream));
             KCHK(launch_iter_end(B.d_insts, B.nsweep, ctx->stream));
         }

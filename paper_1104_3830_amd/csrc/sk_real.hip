@@ -508,7 +508,7 @@ __global__ __launch_bounds__(kRowWaves * kWave) void k_check_rows_real(
 }
 
 // FP64 column partials per row segment (one thread per column, rows of the
-// segment in order), then their sum per column in segment order.
+// segment in order); k_check_sum adds them.
 __global__ __launch_bounds__(256) void k_check_cols_real(const Inst *__restrict__ insts, int inst,
                                                          double *part) {
     const Inst &I = insts[inst];
@@ -516,7 +516,7 @@ __global__ __launch_bounds__(256) void k_check_cols_real(const Inst *__restrict_
     const int j = blockIdx.x * blockDim.x + threadIdx.x;
     const int seg = blockIdx.y;
     if (j >= n) return;
-    const int r0 = seg * I.seg_rows, r1 = min(n, r0 + I.seg_rows);
+    const int r0 = seg * I.chk_seg, r1 = min(n, r0 + I.chk_seg);
     const int par = I.ctl->iter & 1;
     const double p = real_p(I, I.ctl), wref = (double)I.wref;
     const double lv = (double)I.G[j] + (double)I.gam[j];
@@ -528,17 +528,6 @@ __global__ __launch_bounds__(256) void k_check_cols_real(const Inst *__restrict_
         if (lx > kRealNegligible) s += exp(lx);
     }
     part[(int64_t)seg * n + j] = s;
-}
-
-__global__ __launch_bounds__(256) void k_check_cols_sum_real(const Inst *__restrict__ insts, int inst,
-                                                             const double *part, double *csum) {
-    const Inst &I = insts[inst];
-    const int n = I.n;
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= n) return;
-    double s = 0.0;
-    for (int seg = 0; seg < I.nseg; ++seg) s += part[(int64_t)seg * n + j];
-    csum[j] = s;
 }
 
 // ---------------------------------------------------------------- reduced matrix
@@ -640,13 +629,11 @@ hipError_t launch_col_sweep_real(const Inst *d_insts, const ColUnit *d_units, in
 
 hipError_t launch_check_real(const Inst *d_insts, const RowUnit *d_units, int nunits, int grid, int inst,
                              int n, int nseg, double *rsum, double *rmax, double logt, int64_t *counts,
-                             int32_t *hint, double *part, double *csum, hipStream_t st) {
+                             int32_t *hint, double *part, hipStream_t st) {
     hipLaunchKernelGGL(k_check_rows_real, dim3(grid), dim3(kRowWaves * kWave), sizeof(double) * (size_t)n,
                        st, d_insts, d_units, nunits, rsum, rmax, logt, counts, hint);
     hipLaunchKernelGGL(k_check_cols_real, dim3((n + 255) / 256, nseg), dim3(256), 0, st, d_insts, inst,
                        part);
-    hipLaunchKernelGGL(k_check_cols_sum_real, dim3((n + 255) / 256), dim3(256), 0, st, d_insts, inst,
-                       part, csum);
     return hipGetLastError();
 }
 

@@ -105,7 +105,7 @@ sk_status sk_scale_real(sk_ctx *ctx, const float *W, int32_t n, const sk_params 
     rep.threshold_used = NAN;
     const bool empty = (c.err & (ERR_EMPTY_ROW | ERR_EMPTY_COL)) != 0;
     if (!empty) {
-        if ((st = enqueue_check(ctx, B, 0)) != SK_OK) return st;
+        if ((st = enqueue_check(ctx, B)) != SK_OK) return st;
         HIPCHK(ctx, hipMemcpyAsync(ctx->h_checkout, B.d_checkout, 4 * sizeof(double),
                                    hipMemcpyDeviceToHost, ctx->stream));
         HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
@@ -113,7 +113,7 @@ sk_status sk_scale_real(sk_ctx *ctx, const float *W, int32_t n, const sk_params 
         const double pl = params->deform_a > 0.0 ? c.preal : (double)c.p;
         report_from_check(ctx->h_checkout, pl * rep.p_scale, &rep, n, B.h_insts[0].wref);
     }
-    if ((st = copy_potentials_out(ctx, B, 0, potentials)) != SK_OK) return st;
+    if ((st = copy_potentials_out(ctx, B, potentials)) != SK_OK) return st;
     HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
     rep.seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
     if (report) *report = rep;
@@ -177,7 +177,7 @@ sk_status sk_solve_real(sk_ctx *ctx, const float *W, int32_t n, const sk_params 
         // a B with no perfect matching at the last p: lower t tenfold, at most three times
         for (int tries = 0;; ++tries) {
             const CheckCounts cc{std::log(t), B.d_counts, d_hint};
-            sk_status s2 = enqueue_check(ctx, B, 0, &cc);
+            sk_status s2 = enqueue_check(ctx, B, &cc);
             if (s2 != SK_OK) return s2;
             HIPCHK(ctx, PROF(ctx, KID_SCAN, launch_scan(B.d_counts, d_rp, n, ctx->stream, B.d_nnz)));
             HIPCHK(ctx, hipMemcpyAsync(ctx->h_checkout, B.d_checkout, 4 * sizeof(double),
@@ -223,7 +223,7 @@ sk_status sk_solve_real(sk_ctx *ctx, const float *W, int32_t n, const sk_params 
         if (feasible) {
             const double lg = gscale * (rep.ub - wB);
             if (!best.have || lg < best.log_gamma) {
-                sk_status s2 = copy_potentials_out(ctx, B, 0, potentials);
+                sk_status s2 = copy_potentials_out(ctx, B, potentials);
                 if (s2 != SK_OK) return s2;
                 best.have = true;
                 best.p = c.p;
@@ -269,7 +269,7 @@ sk_status sk_solve_real(sk_ctx *ctx, const float *W, int32_t n, const sk_params 
         return fail(ctx, status_of(c), "a row or column of A has no entry");
     }
     if (!best.have) {
-        if ((st = copy_potentials_out(ctx, B, 0, potentials)) != SK_OK) return st;
+        if ((st = copy_potentials_out(ctx, B, potentials)) != SK_OK) return st;
     }
     HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
     sk_report rep;

@@ -30,11 +30,22 @@ struct Batch {
     int count = 0;
     int nmax = 0;
     int nsweep = 0, nsmall = 0;     // instances iterated by the sweeps, and by k_small
+    std::vector<RowUnit> h_mid;     // units of kMidRows rows of the instances iterated by k_mid
+    RowUnit *d_mid = nullptr;
+    // the order of the instances in h_rows, h_ccols and h_fins, and where each
+    // one's units begin there
+    std::vector<int> order, row_at, ccol_at, fin_at;
+    std::vector<ColUnit> h_ccols;   // FP64 check: column units of every instance (batches)
+    ColUnit *d_ccols = nullptr;
+    std::vector<int> chk_end;       // FP64 check in groups that share the scratch: ends in `order`
+    int nsweep_fins = 0;
+    int nmid = 0, mid_wide = 0;     // instances of k_mid; units of those with n > 512 (first in h_mid)
+    bool mid_fold = false;          // launch_mid_pair's fold
     int small_class[kSmallClasses] = {};  // of the latter, those with 64 c < n <= 64 (c + 1)
     int sweep_nmax = 0;  // largest n of the former
     std::vector<Inst> h_insts;
     // row units of every instance (input scan, FP64 check, CSR passes), those
-    // of the swept instances first; the other tables hold swept instances only
+    // of the swept instances first (h_fins alike); h_cols: swept ones only
     std::vector<RowUnit> h_rows;
     int nsweep_rows = 0;
     std::vector<ColUnit> h_cols;
@@ -45,8 +56,7 @@ struct Batch {
     int32_t *d_row_bounds = nullptr;
     ColUnit *d_cols = nullptr;
     FinUnit *d_fins = nullptr;
-    double *d_rsum = nullptr, *d_rmax = nullptr, *d_csum = nullptr;
-    double *d_cpart = nullptr;     // FP64 column partials [nseg][n] of the checked instance
+    double *d_chk = nullptr;       // FP64 check scratch
     Ctl *d_ctl_all = nullptr;      // gathered control blocks (one copy per check)
     double *d_checkout = nullptr;  // [count][4] reduced FP64 checks
     int64_t *d_nnz = nullptr;      // [count] kept entries per instance
@@ -83,7 +93,7 @@ enum KernelId {
     KID_ROW_K_DETECT, KID_COL_K_DETECT, KID_ROW_K_IDLE, KID_COL_K_IDLE,
     KID_FUSED, KID_FUSED_DETECT, KID_FUSED_IDLE,
     KID_NT_PRODUCT, KID_NT_STEP, KID_NT_PRODUCT_IDLE, KID_NT_STEP_IDLE,
-    KID_PAD_COPY, KID_SMALL,
+    KID_PAD_COPY, KID_SMALL, KID_MID,
     KID_COUNT
 };
 extern const char *kKernelNames[KID_COUNT];
@@ -195,6 +205,9 @@ sk_status read_ctl(sk_ctx *ctx, Batch &B);
 sk_status iterate_i16(sk_ctx *ctx, Batch &B, bool chained = false);
 // One launch of up to `budget` iterations of the batch's small instances.
 sk_status iterate_small(sk_ctx *ctx, Batch &B, int budget);
+// At least `count` iterations (an even number of launches) of the instances
+// of k_mid.
+sk_status iterate_mid(sk_ctx *ctx, Batch &B, int count);
 // Iterates until no instance is running (done, error, or paused at a stage
 // end); first_stage: the stage the instances start this call in (launch tags).
 sk_status run_batch_i16(sk_ctx *ctx, Batch &B, const sk_params *prm, int first_stage = 0);
@@ -221,14 +234,17 @@ struct CheckCounts {
     int64_t *counts;
     int32_t *hint;
 };
-sk_status check_fp64(sk_ctx *ctx, Batch &B, int k, sk_report *rep);
-// writes B.d_checkout[k] (and the counts when cc != nullptr)
-sk_status enqueue_check(sk_ctx *ctx, Batch &B, int k, const CheckCounts *cc = nullptr);
+// FP64 check of the batch's one instance: writes B.d_checkout (and the counts
+// when cc != nullptr)
+sk_status enqueue_check(sk_ctx *ctx, Batch &B, const CheckCounts *cc = nullptr);
+// ... of every instance that is not running.
+sk_status enqueue_checks(sk_ctx *ctx, Batch &B);
 // p: the stage's p (ctl.p * pscale); wref: the common shift of a real-valued
 // instance's log-weights (0 for int16 W), added back to the certificate.
 void report_from_check(const double *out4, double p, sk_report *rep, int n = 0, double wref = 0.0);
 void fill_report(const Ctl &c, sk_report *rep);
-sk_status copy_potentials_out(sk_ctx *ctx, Batch &B, int k, void *pot);
+// pot: where the one instance's go; null: every instance's, to Inst::pot
+sk_status copy_potentials_out(sk_ctx *ctx, Batch &B, void *pot);
 // Scales `count` instances with their working memory carved from
 // [arena, arena + arena_bytes) (the context's arena, or the static scratch).
 sk_status scale_impl(sk_ctx *ctx, int count, const int16_t *const *W, const int32_t *n,

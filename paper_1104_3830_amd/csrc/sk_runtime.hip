@@ -43,6 +43,10 @@ TilePlan plan_tiles(int32_t n, int vec8) {
 }
 
 
+// Sizes iterated by k_mid, and its column-partial slots (two copies).
+static bool mid_size(int32_t n) { return n > kSmallN && n <= kMidN; }
+static size_t mid_slots(int32_t n) { return 2 * (size_t)((n + kMidRows - 1) / kMidRows); }
+
 size_t instance_bytes(int32_t n, int vec8, int storage, int fused) {
     TilePlan t = plan_tiles(n, vec8);
     size_t b = 0;
@@ -56,6 +60,10 @@ size_t instance_bytes(int32_t n, int vec8, int storage, int fused) {
     b += align_up(sizeof(float) * n, 256);  // rres
     b += align_up(sizeof(uint32_t) * kRowResSlots * kRowResStride, 256);  // rowres
     if (n > kLdsMaxN) b += align_up(8 * (size_t)pad8(n), 256);  // colpack
+    if (mid_size(n) && storage == SK_W_I16) {
+        b += align_up(sizeof(float) * mid_slots(n) * pad8(n), 256);
+        b += align_up(sizeof(Ctl), 256) + align_up(sizeof(int32_t) * n, 256) + align_up(sizeof(float) * n, 256);
+    }
     if (storage == SK_K_BF16 || storage == SK_K_F32) {
         const size_t es = storage == SK_K_BF16 ? 2 : 4;
         const size_t kp = (size_t)(n + 7) / 8 * 8;
@@ -65,21 +73,38 @@ size_t instance_bytes(int32_t n, int vec8, int storage, int fused) {
     return b;
 }
 
+// Row segments of the FP64 check's column pass.
+static int check_seg_rows(int32_t n, const TilePlan &t) { return n <= kCheckShortN ? kCheckShortSeg : t.seg_rows; }
+static int check_segs(int32_t n, const TilePlan &t) {
+    const int seg = check_seg_rows(n, t);
+    return (n + seg - 1) / seg;
+}
+// Doubles of check scratch for a batch: all instances at once up to 32 MiB
+// (more go in groups), at least the largest instance's.
+static size_t check_scratch(size_t largest, size_t sum) {
+    return std::max(largest, std::min(sum, (size_t)(32 << 20) / sizeof(double)));
+}
+
 // The library's 8-wide copy of a W whose n is not a multiple of 8.
 size_t pad_copy_bytes(int32_t n) {
     return (n % 8) ? align_up(sizeof(int16_t) * (size_t)n * (size_t)pad8(n), 256) : 0;
 }
 
 size_t shared_bytes(int32_t count, const int32_t *n) {
-    int64_t rows = 0, cols = 0, nmax = 0, cpart = 0, fins = 0;
+    int64_t rows = 0, cols = 0, nmax = 0, fins = 0, mids = 0, ccols = 0;
+    size_t chk_max = 0, chk_sum = 0;
     for (int k = 0; k < count; ++k) {
         // an instance takes the 8-wide plan unless its W is misaligned
         // (then the 1-wide plan: no more slots, more column units)
         TilePlan t = plan_tiles(n[k], 1), t1 = plan_tiles(n[k], 0);
-        cpart = std::max<int64_t>(cpart, (int64_t)t.nseg * n[k]);
+        const size_t chk = check_doubles(n[k], check_segs(n[k], t));
+        chk_max = std::max(chk_max, chk);
+        chk_sum += chk;
+        ccols += (int64_t)((n[k] + kColTile8 - 1) / kColTile8) * check_segs(n[k], t);
         rows += (n[k] + kRowWaves - 1) / kRowWaves;
         cols += std::max<int64_t>((int64_t)t.ntiles * t.nseg, (int64_t)t1.ntiles * t1.nseg);
         fins += (n[k] + kFinCols - 1) / kFinCols;
+        if (mid_size(n[k])) mids += (n[k] + kMidRows - 1) / kMidRows;
         nmax = std::max<int64_t>(nmax, n[k]);
     }
     size_t b = 0;
@@ -89,8 +114,9 @@ size_t shared_bytes(int32_t count, const int32_t *n) {
     b += align_up(sizeof(RowUnit) * rows, 256);
     b += align_up(sizeof(ColUnit) * cols, 256);
     b += align_up(sizeof(FinUnit) * fins, 256);
-    b += align_up(sizeof(double) * nmax, 256) * 3;  // FP64 check: rsum, rmax, csum
-    b += align_up(sizeof(double) * (size_t)cpart, 256);  // FP64 column partials
+    if (mids > 0) b += align_up(sizeof(RowUnit) * mids, 256);
+    b += align_up(sizeof(double) * check_scratch(chk_max, chk_sum), 256);
+    if (count > 1) b += align_up(sizeof(ColUnit) * ccols, 256);
     b += align_up(sizeof(int64_t) * (nmax + 1), 256);  // prune row counts
     b += align_up(sizeof(int32_t) * (kMaxRowGrid + 1), 256);  // row-sweep workgroup bounds
     return b;
@@ -106,7 +132,7 @@ const char *kKernelNames[KID_COUNT] = {"init", "row_sweep", "col_sweep", "check_
                                        "col_sweep_k:detect", "row_sweep_k:idle",
                                        "col_sweep_k:idle", "fused", "fused:detect", "fused:idle",
                                        "nt_product", "nt_step", "nt_product:idle",
-                                       "nt_step:idle", "pad_copy", "small"};
+                                       "nt_step:idle", "pad_copy", "small", "mid"};
 
 hipEvent_t Profiler::take() {
     if (!pool.empty()) {
@@ -381,6 +407,8 @@ bool sk::carve_instance(Bump &bump, const int16_t *W, int64_t pitch, int32_t nn,
     I.seg_rows = t.seg_rows;
     I.ntiles = t.ntiles;
     I.tile_cols = t.tile_cols;
+    I.chk_seg = check_seg_rows(nn, t);
+    I.chk_nseg = check_segs(nn, t);
     I.n_p = prm->n_p;
     for (int s = 0; s < prm->n_p; ++s) I.ladder[s] = prm->p_ladder[s];
     I.tol = (float)prm->tol;
@@ -392,8 +420,10 @@ bool sk::carve_instance(Bump &bump, const int16_t *W, int64_t pitch, int32_t nn,
     // by size and options alone, so that a result does not depend on what
     // else is in the batch (the deformed iteration moves p, and with it every
     // entry, each time: it stays with the sweeps)
-    I.small = nn <= kSmallN && !Wr && prm->storage == SK_W_I16 && !prm->fused &&
-              prm->method == SK_SINKHORN && I.deform_a <= 0.0;
+    const bool onchip = !Wr && prm->storage == SK_W_I16 && !prm->fused && prm->method == SK_SINKHORN &&
+                        I.deform_a <= 0.0;
+    I.small = onchip && nn <= kSmallN;
+    I.mid = onchip && mid_size(nn);
     for (int b = 0; b < 2; ++b) {
         I.F[b] = bump.take<int32_t>(nn);
         I.phi[b] = bump.take<float>(nn);
@@ -401,7 +431,7 @@ bool sk::carve_instance(Bump &bump, const int16_t *W, int64_t pitch, int32_t nn,
     I.G = bump.take<int32_t>(nn);
     I.gam = bump.take<float>(nn);
     const size_t slots = I.fused ? std::max(t.nseg, kFusedSlots) : t.nseg;
-    I.colpart = bump.take<float>(slots * nn);
+    I.colpart = bump.take<float>(I.mid ? mid_slots(nn) * pad8(nn) : slots * nn);
     I.rescue = bump.take<uint32_t>(nn);
     I.ctl = bump.take<Ctl>(1);
     const int nrows_units = (nn + kRowWaves - 1) / kRowWaves;
@@ -418,6 +448,12 @@ bool sk::carve_instance(Bump &bump, const int16_t *W, int64_t pitch, int32_t nn,
     if (!I.F[0] || !I.F[1] || !I.phi[0] || !I.phi[1] || !I.G || !I.gam || !I.colpart ||
         !I.rescue || !I.ctl)
         return false;
+    if (I.mid) {
+        I.ctl2 = bump.take<Ctl>(1);
+        I.G2 = bump.take<int32_t>(nn);
+        I.gam2 = bump.take<float>(nn);
+        if (!I.ctl2 || !I.G2 || !I.gam2) return false;
+    }
     I.kpitch = (nn + 7) / 8 * 8;
     if (prm->storage != SK_W_I16) {
         const size_t es = prm->storage == SK_K_BF16 ? 2 : 4;
@@ -444,27 +480,82 @@ sk_status sk::finish_tables(sk_ctx *ctx, Bump &bump, Batch &B) {
     B.h_rows.clear();
     B.h_cols.clear();
     B.h_fins.clear();
+    B.h_ccols.clear();
+    B.order.clear();
+    B.row_at.assign((size_t)B.count + 1, 0);
+    B.ccol_at.assign((size_t)B.count + 1, 0);
+    B.fin_at.assign((size_t)B.count + 1, 0);
     B.nmax = B.sweep_nmax = 0;
     B.nsweep = B.nsmall = 0;
     for (int &c : B.small_class) c = 0;
-    int64_t cpart = 0;
+    B.h_mid.clear();
+    B.nmid = B.mid_wide = 0;
     for (int k = 0; k < B.count; ++k) {
         const Inst &I = B.h_insts[k];
-        cpart = std::max<int64_t>(cpart, (int64_t)I.nseg * I.n);
         B.nmax = std::max(B.nmax, I.n);
         if (I.small) {
             B.nsmall += 1;
             B.small_class[(I.n - 1) / kWave] += 1;
-            continue;
         }
-        for (int r = 0; r < I.n; r += kRowWaves) B.h_rows.push_back(RowUnit{k, r});
+        if (I.mid) B.h_insts[B.nmid++].mid_idx = k;
+        if (I.small || I.mid) continue;
+        B.order.push_back(k);
         for (int s = 0; s < I.nseg; ++s)
             for (int tt = 0; tt < I.ntiles; ++tt) B.h_cols.push_back(ColUnit{k, tt, s, 0});
-        for (int g = 0; g * kFinCols < I.n; ++g) B.h_fins.push_back(FinUnit{k, g});
         B.sweep_nmax = std::max(B.sweep_nmax, I.n);
         B.h_insts[B.nsweep++].sweep_idx = k;
     }
-    B.nsweep_rows = (int)B.h_rows.size();
+    for (int k = 0; k < B.count; ++k)
+        if (B.h_insts[k].small || B.h_insts[k].mid) B.order.push_back(k);
+    size_t chk_max = 0, chk_sum = 0;
+    for (int q = 0; q < B.count; ++q) {
+        const int k = B.order[q];
+        const Inst &I = B.h_insts[k];
+        if (q == B.nsweep) {
+            B.nsweep_rows = (int)B.h_rows.size();
+            B.nsweep_fins = (int)B.h_fins.size();
+        }
+        B.h_insts[q].ord_idx = k;
+        B.row_at[q] = (int)B.h_rows.size();
+        B.ccol_at[q] = (int)B.h_ccols.size();
+        B.fin_at[q] = (int)B.h_fins.size();
+        for (int r = 0; r < I.n; r += kRowWaves) B.h_rows.push_back(RowUnit{k, r});
+        for (int g = 0; g * kFinCols < I.n; ++g) B.h_fins.push_back(FinUnit{k, g});
+        if (B.count > 1)
+            for (int s = 0; s < I.chk_nseg; ++s)
+                for (int tt = 0; tt * kColTile8 < I.n; ++tt) B.h_ccols.push_back(ColUnit{k, tt, s, 0});
+        const size_t chk = check_doubles(I.n, I.chk_nseg);
+        chk_max = std::max(chk_max, chk);
+        chk_sum += chk;
+    }
+    B.row_at[B.count] = (int)B.h_rows.size();
+    B.ccol_at[B.count] = (int)B.h_ccols.size();
+    B.fin_at[B.count] = (int)B.h_fins.size();
+    if (B.nsweep == B.count) {
+        B.nsweep_rows = (int)B.h_rows.size();
+        B.nsweep_fins = (int)B.h_fins.size();
+    }
+    // a run of blocks per workgroup such that each launch has about the two
+    // workgroups per compute unit that are resident at once (the blocks of a
+    // run share the staging of the column potentials)
+    int mblocks[2] = {0, 0};
+    for (int q = 0; q < B.nmid; ++q) {
+        const int nn = B.h_insts[B.h_insts[q].mid_idx].n;
+        mblocks[nn > 512] += (nn + kMidRows - 1) / kMidRows;
+    }
+    B.mid_fold = mblocks[0] + mblocks[1] <= kMidFoldUnits;
+    for (const bool wide : {true, false}) {
+        const int run =
+            B.mid_fold ? 1 : std::max(1, std::min(kMidRun, (mblocks[wide] + 2 * ctx->num_cus - 1) / (2 * ctx->num_cus)));
+        for (int q = 0; q < B.nmid; ++q) {
+            const int k = B.h_insts[q].mid_idx, nn = B.h_insts[k].n;
+            if ((nn > 512) != wide) continue;
+            const int nb = (nn + kMidRows - 1) / kMidRows;
+            for (int b = 0; b < nb; b += run)
+                B.h_mid.push_back(RowUnit{k, kMidRows * b | std::min(run, nb - b) << 16});
+        }
+        if (wide) B.mid_wide = (int)B.h_mid.size();
+    }
     int at[kSmallClasses];
     for (int c = kSmallClasses - 1, first = 0; c >= 0; --c) {
         at[c] = first;
@@ -472,9 +563,7 @@ sk_status sk::finish_tables(sk_ctx *ctx, Bump &bump, Batch &B) {
     }
     for (int k = 0; k < B.count; ++k) {
         const Inst &I = B.h_insts[k];
-        if (!I.small) continue;
-        for (int r = 0; r < I.n; r += kRowWaves) B.h_rows.push_back(RowUnit{k, r});
-        B.h_insts[at[(I.n - 1) / kWave]++].small_idx = k;
+        if (I.small) B.h_insts[at[(I.n - 1) / kWave]++].small_idx = k;
     }
     B.d_insts = bump.take<Inst>(B.count);
     B.d_ctl_all = bump.take<Ctl>(B.count);
@@ -483,14 +572,33 @@ sk_status sk::finish_tables(sk_ctx *ctx, Bump &bump, Batch &B) {
     B.d_rows = bump.take<RowUnit>(B.h_rows.size());
     B.d_cols = bump.take<ColUnit>(B.h_cols.size());
     B.d_fins = bump.take<FinUnit>(B.h_fins.size());
-    B.d_rsum = bump.take<double>(B.nmax);
-    B.d_rmax = bump.take<double>(B.nmax);
-    B.d_csum = bump.take<double>(B.nmax);
+    B.d_mid = B.h_mid.empty() ? nullptr : bump.take<RowUnit>(B.h_mid.size());
     B.d_counts = bump.take<int64_t>(B.nmax + 1);
-    B.d_cpart = bump.take<double>(cpart);
-    if (!B.d_insts || !B.d_rows || !B.d_cols || !B.d_fins || !B.d_rsum || !B.d_rmax || !B.d_csum ||
-        !B.d_counts || !B.d_cpart || !B.d_ctl_all || !B.d_checkout || !B.d_nnz)
+    B.d_ccols = B.h_ccols.empty() ? nullptr : bump.take<ColUnit>(B.h_ccols.size());
+    if ((!B.h_mid.empty() && !B.d_mid) || (!B.h_ccols.empty() && !B.d_ccols) || !B.d_insts || !B.d_rows || !B.d_cols ||
+        !B.d_fins || !B.d_counts || !B.d_ctl_all || !B.d_checkout || !B.d_nnz)
         return fail(ctx, SK_ENOMEM, "arena too small for the batch tables");
+    // the check's scratch: consecutive instances share it group by group
+    size_t chk_cap = check_scratch(chk_max, chk_sum);
+    B.d_chk = bump.take<double>(chk_cap);
+    if (!B.d_chk) {
+        chk_cap = chk_max;
+        B.d_chk = bump.take<double>(chk_cap);
+    }
+    if (!B.d_chk) return fail(ctx, SK_ENOMEM, "arena too small for the batch tables");
+    B.chk_end.clear();
+    size_t chk_used = 0;
+    for (int q = 0; q < B.count; ++q) {
+        Inst &I = B.h_insts[B.order[q]];
+        const size_t chk = check_doubles(I.n, I.chk_nseg);
+        if (chk_used + chk > chk_cap) {
+            B.chk_end.push_back(q);
+            chk_used = 0;
+        }
+        I.chk = B.d_chk + chk_used;
+        chk_used += chk;
+    }
+    B.chk_end.push_back(B.count);
     // grids: row sweep stages pad8(n) columns of potentials (8 B each) in LDS
     // (above kLdsMaxN it reads them from the instance's packed buffer)
     const size_t lds = B.nmax > kLdsMaxN ? 0 : sizeof(float2) * (size_t)pad8(B.nmax);
@@ -538,7 +646,7 @@ sk_status sk::finish_tables(sk_ctx *ctx, Bump &bump, Batch &B) {
         if (!B.d_row_bounds) return fail(ctx, SK_ENOMEM, "arena too small for the batch tables");
     }
     B.col_grid = (int)std::max<size_t>(1, std::min<size_t>(B.h_cols.size(), (size_t)ctx->num_cus * 8));
-    B.fin_grid = (int)std::max<size_t>(1, std::min<size_t>(B.h_fins.size(), (size_t)ctx->num_cus * 4));
+    B.fin_grid = (int)std::max<size_t>(1, std::min<size_t>(B.nsweep_fins, (size_t)ctx->num_cus * 4));
     return SK_OK;
 }
 
@@ -560,12 +668,17 @@ sk_status sk::upload_batch(sk_ctx *ctx, Batch &B) {
     HIPCHK(ctx, hipMemcpyAsync(B.d_row_bounds, B.h_row_bounds.data(),
                                sizeof(int32_t) * B.h_row_bounds.size(), hipMemcpyHostToDevice,
                                ctx->stream));
-    if (B.nsweep > 0) {
+    HIPCHK(ctx, hipMemcpyAsync(B.d_fins, B.h_fins.data(), sizeof(FinUnit) * B.h_fins.size(),
+                               hipMemcpyHostToDevice, ctx->stream));
+    if (!B.h_ccols.empty())
+        HIPCHK(ctx, hipMemcpyAsync(B.d_ccols, B.h_ccols.data(), sizeof(ColUnit) * B.h_ccols.size(),
+                                   hipMemcpyHostToDevice, ctx->stream));
+    if (B.nsweep > 0)
         HIPCHK(ctx, hipMemcpyAsync(B.d_cols, B.h_cols.data(), sizeof(ColUnit) * B.h_cols.size(),
                                    hipMemcpyHostToDevice, ctx->stream));
-        HIPCHK(ctx, hipMemcpyAsync(B.d_fins, B.h_fins.data(), sizeof(FinUnit) * B.h_fins.size(),
+    if (!B.h_mid.empty())
+        HIPCHK(ctx, hipMemcpyAsync(B.d_mid, B.h_mid.data(), sizeof(RowUnit) * B.h_mid.size(),
                                    hipMemcpyHostToDevice, ctx->stream));
-    }
     bool pads = false;
     for (const Inst &I : B.h_insts) pads |= I.Wsrc != nullptr;
     if (pads)
@@ -578,18 +691,9 @@ sk_status sk::upload_batch(sk_ctx *ctx, Batch &B) {
 sk_status sk::start_batch(sk_ctx *ctx, Batch &B, const sk_params *prm, void *const *pot_in) {
     HIPCHK(ctx, launch_reset_ctl(B.d_insts, nullptr, B.count, ctx->stream));
     if (prm->warm_start) {
-        for (int k = 0; k < B.count; ++k) {
-            const int nn = B.h_insts[k].n;
-            const char *src = (const char *)pot_in[k];
-            HIPCHK(ctx, hipMemcpyAsync(B.h_insts[k].F[0], src, 4 * (size_t)nn,
-                                       hipMemcpyDeviceToDevice, ctx->stream));
-            HIPCHK(ctx, hipMemcpyAsync(B.h_insts[k].phi[0], src + 4 * (size_t)nn, 4 * (size_t)nn,
-                                       hipMemcpyDeviceToDevice, ctx->stream));
-            HIPCHK(ctx, hipMemcpyAsync(B.h_insts[k].G, src + 8 * (size_t)nn, 4 * (size_t)nn,
-                                       hipMemcpyDeviceToDevice, ctx->stream));
-            HIPCHK(ctx, hipMemcpyAsync(B.h_insts[k].gam, src + 12 * (size_t)nn, 4 * (size_t)nn,
-                                       hipMemcpyDeviceToDevice, ctx->stream));
-        }
+        const bool one = B.count == 1;
+        HIPCHK(ctx, launch_copy_pot(B.d_insts, one ? nullptr : B.d_fins, 0, (int)B.h_fins.size(),
+                                    one ? pot_in[0] : nullptr, 1, ctx->stream));
     }
     if (B.h_insts[0].Wr)
         HIPCHK(ctx, PROF(ctx, KID_INIT, launch_init_real(B.d_insts, B.d_rows, (int)B.h_rows.size(),
@@ -620,7 +724,7 @@ sk_status sk::iterate_i16(sk_ctx *ctx, Batch &B, bool chained) {
         const Inst &I = B.h_insts[0];
         HIPCHK(ctx, PROF(ctx, KID_FUSED, launch_fused(B.d_insts, 0, I.n, I.fused_grid, SK_W_I16,
                                                       I.nt, ctx->stream)));
-        HIPCHK(ctx, launch_col_finalize(B.d_insts, B.d_fins, (int)B.h_fins.size(), B.fin_grid,
+        HIPCHK(ctx, launch_col_finalize(B.d_insts, B.d_fins, B.nsweep_fins, B.fin_grid,
                                         kFinOnePass, ctx->stream));
         HIPCHK(ctx, launch_iter_end(B.d_insts, B.nsweep, ctx->stream));
         pf.iter_end_stamp = -1;
@@ -654,8 +758,7 @@ sk_status sk::iterate_i16(sk_ctx *ctx, Batch &B, bool chained) {
                                      B.sweep_nmax <= kShortRowN, ctx->stream, e2));
     pf.add(KID_ROW, s0, s1);
     pf.add(KID_COL, s1, s2);
-    HIPCHK(ctx, launch_col_finalize(B.d_insts, B.d_fins, (int)B.h_fins.size(), B.fin_grid, 0,
-                                    ctx->stream));
+    HIPCHK(ctx, launch_col_finalize(B.d_insts, B.d_fins, B.nsweep_fins, B.fin_grid, 0, ctx->stream));
     hipEvent_t e3 = pf.kernel_stamp(&s3);
     HIPCHK(ctx, launch_iter_end(B.d_insts, B.nsweep, ctx->stream, e3));
     pf.iter_end_stamp = s3;
@@ -665,6 +768,15 @@ sk_status sk::iterate_i16(sk_ctx *ctx, Batch &B, bool chained) {
 sk_status sk::iterate_small(sk_ctx *ctx, Batch &B, int budget) {
     if (B.nsmall == 0) return SK_OK;
     HIPCHK(ctx, PROF(ctx, KID_SMALL, launch_small(B.d_insts, B.small_class, budget, ctx->stream)));
+    return SK_OK;
+}
+
+sk_status sk::iterate_mid(sk_ctx *ctx, Batch &B, int count) {
+    if (B.h_mid.empty()) return SK_OK;
+    for (int k = 0; k < count; k += 2)
+        HIPCHK(ctx, PROF(ctx, KID_MID, launch_mid_pair(B.d_insts, B.count == 1 ? nullptr : B.d_mid, B.mid_wide,
+                                                  (int)B.h_mid.size() - B.mid_wide, B.nmid, B.mid_fold,
+                                                  ctx->stream)));
     return SK_OK;
 }
 
@@ -689,7 +801,7 @@ sk_status sk::run_batch_i16(sk_ctx *ctx, Batch &B, const sk_params *prm, int fir
     // block of a paused stage is sized by the previous stage's iterations.
     constexpr int kTailBlock = 8;
     int blk = check;
-    bool swept = B.nsweep > 0;  // the sweeps have a running instance
+    bool swept = B.nsweep > 0, mid = !B.h_mid.empty();  // they have a running instance
     if (B.count == 1 && B.h_insts[0].pause && first_stage > 0)
         blk = (int)std::min<int64_t>(check, std::max<int64_t>(
                                                 4, ctx->h_ctl[0].stage_iters[first_stage - 1] + 2));
@@ -699,20 +811,21 @@ sk_status sk::run_batch_i16(sk_ctx *ctx, Batch &B, const sk_params *prm, int fir
                 sk_status s = iterate_i16(ctx, B, k > 0);
                 if (s != SK_OK) return s;
             }
-        sk_status s = iterate_small(ctx, B, kSmallBudget);
+        sk_status s = mid ? iterate_mid(ctx, B, blk) : SK_OK;
+        if (s == SK_OK) s = iterate_small(ctx, B, kSmallBudget);
         if (s != SK_OK) return s;
         // every running instance has moved on by its block
-        launched += swept ? blk : kSmallBudget;
+        launched += swept || mid ? blk : kSmallBudget;
         if ((s = read_ctl(ctx, B)) != SK_OK) return s;
         bool running = false, tail = true;
-        swept = false;
+        swept = mid = false;
         for (int k = 0; k < B.count; ++k) {
             const Ctl &c = ctx->h_ctl[k];
             if (c.state != ST_RUNNING) continue;
             running = true;
             const Inst &I = B.h_insts[k];
             if (I.small) continue;
-            swept = true;
+            (I.mid ? mid : swept) = true;
             // (the deformed iteration is one long stage: full blocks)
             const bool last = I.deform_a <= 0.0 && c.stage + 1 >= I.n_p;
             tail &= last || I.pause;
@@ -727,7 +840,7 @@ sk_status sk::run_batch_i16(sk_ctx *ctx, Batch &B, const sk_params *prm, int fir
         std::vector<int64_t> detect;
         int64_t working = 0;
         for (int k = 0; k < B.count; ++k) {
-            if (B.h_insts[k].small) continue;
+            if (B.h_insts[k].small || B.h_insts[k].mid) continue;
             const Ctl &c = ctx->h_ctl[k];
             int64_t t = 0;
             for (int s = first_stage; s <= std::min(c.stage, prm->n_p - 1); ++s) {
@@ -757,37 +870,64 @@ sk_status sk::run_batch_i16(sk_ctx *ctx, Batch &B, const sk_params *prm, int fir
     return SK_OK;
 }
 
-// FP64 recheck of instance k (enqueued): row and column sums of the balanced
-// matrix and the certificate terms, reduced on the device into B.d_checkout[k].
-sk_status sk::enqueue_check(sk_ctx *ctx, Batch &B, int k, const CheckCounts *cc) {
-    const Inst &I = B.h_insts[k];
+// FP64 recheck of the batch's one instance (enqueued): row and column sums of
+// the balanced matrix and the certificate terms, reduced on the device into
+// B.d_checkout.
+sk_status sk::enqueue_check(sk_ctx *ctx, Batch &B, const CheckCounts *cc) {
+    const Inst &I = B.h_insts[0];
     const int nn = I.n;
-    size_t first = 0;
-    while (first < B.h_rows.size() && B.h_rows[first].inst != k) ++first;
-    const int nunits = (nn + kRowWaves - 1) / kRowWaves;
+    const int nunits = (int)B.h_rows.size(), nfins = (int)B.h_fins.size();
     const int grid = std::min(nunits, ctx->num_cus * 2);
     if (I.Wr) {
         HIPCHK(ctx, PROF(ctx, KID_CHECK_ROWS,
-                         launch_check_real(B.d_insts, B.d_rows + first, nunits, grid, k, nn, I.nseg,
-                                           B.d_rsum, B.d_rmax, cc ? cc->logt : 0.0,
+                         launch_check_real(B.d_insts, B.d_rows, nunits, grid, 0, nn, I.chk_nseg, I.chk,
+                                           I.chk + check_stride(nn), cc ? cc->logt : 0.0,
                                            cc ? cc->counts : nullptr, cc ? cc->hint : nullptr,
-                                           B.d_cpart, B.d_csum, ctx->stream)));
-        HIPCHK(ctx, launch_check_reduce(B.d_insts, k, B.d_rsum, B.d_rmax, B.d_csum,
-                                        B.d_checkout + 4 * (size_t)k, ctx->stream));
+                                           I.chk + 3 * check_stride(nn), ctx->stream)));
+        HIPCHK(ctx, launch_check_sums(B.d_insts, nullptr, 0, nfins, 0, 1, 0, B.d_checkout, ctx->stream));
         return SK_OK;
     }
     // n > kLdsMaxN: the row pass reads (G_j, gam_j) packed in I.colpack
     const int gcol = I.colpack != nullptr;
-    if (gcol) HIPCHK(ctx, launch_col_pack(B.d_insts, k, nn, 1, ctx->stream));
+    if (gcol) HIPCHK(ctx, launch_col_pack(B.d_insts, 0, nn, 1, ctx->stream));
     HIPCHK(ctx, PROF(ctx, KID_CHECK_ROWS,
-                     launch_check_rows(B.d_insts, B.d_rows + first, nunits, grid, B.d_rsum,
-                                       B.d_rmax, cc ? cc->logt : 0.0, cc ? cc->counts : nullptr,
-                                       cc ? cc->hint : nullptr, gq_lds_bytes(nn), I.nt, gcol,
-                                       ctx->stream)));
-    HIPCHK(ctx, PROF(ctx, KID_CHECK_COLS, launch_check_cols(B.d_insts, k, nn, I.nseg, I.vec8,
-                                                            B.d_cpart, B.d_csum, I.nt, ctx->stream)));
-    HIPCHK(ctx, launch_check_reduce(B.d_insts, k, B.d_rsum, B.d_rmax, B.d_csum,
-                                    B.d_checkout + 4 * (size_t)k, ctx->stream));
+                     launch_check_rows(B.d_insts, B.d_rows, nunits, grid, 0, cc ? cc->logt : 0.0,
+                                       cc ? cc->counts : nullptr, cc ? cc->hint : nullptr, gq_lds_bytes(nn), I.nt,
+                                       gcol, ctx->stream)));
+    const int ncols = (nn + kColTile8 - 1) / kColTile8 * I.chk_nseg;
+    HIPCHK(ctx, PROF(ctx, KID_CHECK_COLS,
+                     launch_check_cols(B.d_insts, nullptr, 0, ncols, 0, I.nt, ctx->stream)));
+    HIPCHK(ctx, launch_check_sums(B.d_insts, nullptr, 0, nfins, 0, 1, 0, B.d_checkout, ctx->stream));
+    return SK_OK;
+}
+
+// The same for every instance of a batch (int16 W, n <= kLdsMaxN) that is not
+// running, a launch of each kernel per group of instances that fits the
+// scratch (separate launches per instance: 40 us each, 20 ms of the 28 ms of a
+// 512-instance planted batch).
+sk_status sk::enqueue_checks(sk_ctx *ctx, Batch &B) {
+    if (B.count == 1 && B.h_insts[0].colpack) return enqueue_check(ctx, B);
+    int q0 = 0;
+    for (const int q1 : B.chk_end) {
+        int nmax = 0;
+        for (int q = q0; q < q1; ++q) nmax = std::max(nmax, B.h_insts[B.order[q]].n);
+        const int nrows = B.row_at[q1] - B.row_at[q0];
+        const int nt = B.h_insts[0].nt;  // the same for the whole batch
+        // short rows: two workgroups per CU (their column data fits twice)
+        const int grid = std::min(nrows, ctx->num_cus * 2);
+        HIPCHK(ctx, PROF(ctx, KID_CHECK_ROWS,
+                         launch_check_rows(B.d_insts, B.d_rows + B.row_at[q0], nrows, grid, 1, 0.0, nullptr, nullptr,
+                                           gq_lds_bytes(nmax), nt, 0, ctx->stream)));
+        const bool one = B.count == 1;
+        const int ncols = one ? (nmax + kColTile8 - 1) / kColTile8 * B.h_insts[0].chk_nseg
+                              : B.ccol_at[q1] - B.ccol_at[q0];
+        HIPCHK(ctx, PROF(ctx, KID_CHECK_COLS,
+                         launch_check_cols(B.d_insts, one ? nullptr : B.d_ccols + B.ccol_at[q0], 0, ncols, 1, nt,
+                                           ctx->stream)));
+        HIPCHK(ctx, launch_check_sums(B.d_insts, B.d_fins + B.fin_at[q0], 0, B.fin_at[q1] - B.fin_at[q0], q0, q1 - q0,
+                                      1, B.d_checkout, ctx->stream));
+        q0 = q1;
+    }
     return SK_OK;
 }
 
@@ -801,16 +941,6 @@ void sk::report_from_check(const double *o, double p, sk_report *rep, int n, dou
     rep->ub = (o[2] - o[3]) / p + (double)n * wref;
 }
 
-sk_status sk::check_fp64(sk_ctx *ctx, Batch &B, int k, sk_report *rep) {
-    sk_status st = enqueue_check(ctx, B, k);
-    if (st != SK_OK) return st;
-    HIPCHK(ctx, hipMemcpyAsync(ctx->h_checkout + 4 * (size_t)k, B.d_checkout + 4 * (size_t)k,
-                               4 * sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
-    HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
-    report_from_check(ctx->h_checkout + 4 * (size_t)k, ctx->h_ctl[k].p, rep);
-    return SK_OK;
-}
-
 void sk::fill_report(const Ctl &c, sk_report *rep) {
     rep->residual_fp32 = c.last_res;
     rep->iters_total = c.iters_total;
@@ -819,18 +949,9 @@ void sk::fill_report(const Ctl &c, sk_report *rep) {
     rep->stages_capped = c.capped;
 }
 
-sk_status sk::copy_potentials_out(sk_ctx *ctx, Batch &B, int k, void *pot) {
-    const Inst &I = B.h_insts[k];
-    const int nn = I.n;
-    const int par = ctx->h_ctl[k].iter & 1;
-    char *dst = (char *)pot;
-    HIPCHK(ctx, hipMemcpyAsync(dst, I.F[par], 4 * (size_t)nn, hipMemcpyDeviceToDevice, ctx->stream));
-    HIPCHK(ctx, hipMemcpyAsync(dst + 4 * (size_t)nn, I.phi[par], 4 * (size_t)nn,
-                               hipMemcpyDeviceToDevice, ctx->stream));
-    HIPCHK(ctx, hipMemcpyAsync(dst + 8 * (size_t)nn, I.G, 4 * (size_t)nn, hipMemcpyDeviceToDevice,
-                               ctx->stream));
-    HIPCHK(ctx, hipMemcpyAsync(dst + 12 * (size_t)nn, I.gam, 4 * (size_t)nn,
-                               hipMemcpyDeviceToDevice, ctx->stream));
+sk_status sk::copy_potentials_out(sk_ctx *ctx, Batch &B, void *pot) {
+    const bool one = pot != nullptr;
+    HIPCHK(ctx, launch_copy_pot(B.d_insts, one ? nullptr : B.d_fins, 0, (int)B.h_fins.size(), pot, 0, ctx->stream));
     return SK_OK;
 }
 
@@ -886,6 +1007,7 @@ sk_status sk::scale_impl(sk_ctx *ctx, int count, const int16_t *const *W, const 
     Bump bump{arena, arena_bytes};
     Batch &B = ctx->scratch_batch;
     if ((st = plan_batch(ctx, bump, count, W, pitch.data(), n, prm, B)) != SK_OK) return st;
+    for (int k = 0; k < count; ++k) B.h_insts[k].pot = pot[k];
     if ((st = upload_batch(ctx, B)) != SK_OK) return st;
     if ((st = start_batch(ctx, B, prm, pot)) != SK_OK) return st;
     if (prm->method == SK_NEWTON) {
@@ -900,16 +1022,15 @@ sk_status sk::scale_impl(sk_ctx *ctx, int count, const int16_t *const *W, const 
     sk_status result = SK_OK;
     // FP64 checks of every instance, reduced on the device; one copy back
     bool any_check = false;
-    for (int k = 0; k < count; ++k) {
-        if (ctx->h_ctl[k].err & (ERR_EMPTY_ROW | ERR_EMPTY_COL)) continue;
-        if ((st = enqueue_check(ctx, B, k)) != SK_OK) return st;
-        any_check = true;
-    }
+    for (int k = 0; k < count; ++k) any_check |= !(ctx->h_ctl[k].err & (ERR_EMPTY_ROW | ERR_EMPTY_COL));
     if (any_check) {
+        st = count == 1 ? enqueue_check(ctx, B) : enqueue_checks(ctx, B);
+        if (st != SK_OK) return st;
         HIPCHK(ctx, hipMemcpyAsync(ctx->h_checkout, B.d_checkout, sizeof(double) * 4 * count,
                                    hipMemcpyDeviceToHost, ctx->stream));
-        HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
     }
+    if ((st = copy_potentials_out(ctx, B, count == 1 ? pot[0] : nullptr)) != SK_OK) return st;
+    HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
     for (int k = 0; k < count; ++k) {
         const Ctl &c = ctx->h_ctl[k];
         sk_report rep;
@@ -923,14 +1044,12 @@ sk_status sk::scale_impl(sk_ctx *ctx, int count, const int16_t *const *W, const 
                 rep.col_residual_fp64 = ctx->k_res_cols;
             }
         }
-        if ((st = copy_potentials_out(ctx, B, k, pot[k])) != SK_OK) return st;
         rep.seconds = 0;
         if (reports) reports[k] = rep;
         sk_status sk = status_of(c);
         if (sk == SK_ENOSUPPORT || sk == SK_EDEVICE) result = sk;
         else if (sk == SK_ENOCONV && result == SK_OK) result = SK_ENOCONV;
     }
-    HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
     const double secs =
         std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
     if (reports)

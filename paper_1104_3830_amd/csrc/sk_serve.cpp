@@ -108,7 +108,7 @@ static void release_staging(Server *S, Request *r) {
 
 // Iterations per tick of the small instances (about as long as a tick of the
 // sweeps' iterations).
-static const int kServeSmallIters = 256;
+static const int kServeSmallIters = 64;
 
 static const size_t kTablesBytes = size_t(64) << 20;
 
@@ -253,7 +253,9 @@ static sk_status retire_all(Server *S, const std::vector<int> &fin) {
     std::vector<size_t> rp_off(m, 0), rp_len(m, 0);
     std::vector<char> live(m, 0);
     hipError_t e = hipSuccess;
-    sk_status st = SK_OK;
+    std::vector<int> first_row(B.count);
+    for (int q = 0; q < B.count; ++q) first_row[B.order[q]] = B.row_at[q];
+    sk_status st = enqueue_checks(ctx, B);
     for (size_t q = 0; q < m && st == SK_OK && e == hipSuccess; ++q) {
         const int k = fin[q];
         Request *r = S->active[k];
@@ -274,10 +276,7 @@ static sk_status retire_all(Server *S, const std::vector<int> &fin) {
             }
         }
         live[q] = 1;
-        st = enqueue_check(ctx, B, k);
-        if (st != SK_OK) break;
-        size_t first = 0;
-        while (first < B.h_rows.size() && B.h_rows[first].inst != k) ++first;
+        const int first = first_row[k];
         const int nunits = (r->n + kRowWaves - 1) / kRowWaves;
         const int grid = std::min(nunits, ctx->num_cus * 2);
         const double logt = std::log(r->prm.threshold);
@@ -319,8 +318,7 @@ static sk_status retire_all(Server *S, const std::vector<int> &fin) {
             }
             int32_t *d_col = (int32_t *)(ctx->arena + cw_off[q]);
             int16_t *d_w = (int16_t *)(ctx->arena + cw_off[q] + col_bytes);
-            size_t first = 0;
-            while (first < B.h_rows.size() && B.h_rows[first].inst != k) ++first;
+            const int first = first_row[k];
             const int nunits = (r->n + kRowWaves - 1) / kRowWaves;
             const int grid = std::min(nunits, ctx->num_cus * 2);
             e = launch_prune_fill(B.d_insts, B.d_rows + first, nunits, grid,
@@ -442,6 +440,7 @@ static void serve_loop(Server *S) {
         }
         for (int it = 0; it < S->iters_per_tick && st == SK_OK && e == hipSuccess; ++it)
             if (S->B.nsweep > 0) st = iterate_i16(ctx, S->B);
+        if (st == SK_OK && e == hipSuccess) st = iterate_mid(ctx, S->B, S->iters_per_tick / 2);
         if (st == SK_OK && e == hipSuccess) st = iterate_small(ctx, S->B, kServeSmallIters);
         if (st == SK_OK && e == hipSuccess) st = read_ctl(ctx, S->B);
         if (st != SK_OK || e != hipSuccess) {

@@ -86,6 +86,9 @@ __device__ __forceinline__ void small_run(const Inst &I, SmallLds<C, T> &L, unsi
         G = I.G[colj];
         gam = I.gam[colj];
     }
+    // a caller's starting potentials may split their logarithm in any way
+    unit_frac(F, phi);
+    unit_frac(G, gam);
     // entries outside the matrix are absent ones
     unsigned wp[WLDS ? 1 : NP];
 #pragma unroll

@@ -169,7 +169,7 @@ extern "C" sk_status sk_solve(sk_ctx *ctx, const int16_t *W, int32_t n, const sk
         // FP64 certificate, row lengths of B at t and their scan: one sync
         double t = params->threshold;
         const CheckCounts cc{std::log(t), B.d_counts, d_hint};
-        sk_status s2 = enqueue_check(ctx, B, 0, &cc);
+        sk_status s2 = enqueue_check(ctx, B, &cc);
         if (s2 != SK_OK) return s2;
         HIPCHK(ctx, PROF(ctx, KID_SCAN, launch_scan(B.d_counts, d_rp, n, ctx->stream, B.d_nnz)));
         HIPCHK(ctx, hipMemcpyAsync(ctx->h_checkout, B.d_checkout, 4 * sizeof(double),
@@ -189,7 +189,7 @@ extern "C" sk_status sk_solve(sk_ctx *ctx, const int16_t *W, int32_t n, const sk
         if (r.feasible) {
             r.log_gamma = r.rep.ub - (double)r.weight;
             if (!have_best || r.log_gamma < best.log_gamma) {
-                if ((s2 = copy_potentials_out(ctx, B, 0, potentials)) != SK_OK) return s2;
+                if ((s2 = copy_potentials_out(ctx, B, potentials)) != SK_OK) return s2;
                 best = std::move(r);
                 have_best = true;
             }
@@ -246,7 +246,7 @@ extern "C" sk_status sk_solve(sk_ctx *ctx, const int16_t *W, int32_t n, const sk
         return fail(ctx, status_of(c), "a row or column of A has no entry");
     }
     if (!have_best) {
-        if ((st = copy_potentials_out(ctx, B, 0, potentials)) != SK_OK) return st;
+        if ((st = copy_potentials_out(ctx, B, potentials)) != SK_OK) return st;
     }
     HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
     sk_report rep;

@@ -72,6 +72,24 @@ __device__ __forceinline__ double wave_sums16(Fn f, int lane) {
     return s;
 }
 
+// The same for 8 values: lane l gets the sum of f(l / 8).
+template <class Fn>
+__device__ __forceinline__ double wave_sums8(Fn f, int lane) {
+    double a[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const float x = f(k), y = f(k + 4);
+        a[k] = swap_add32(x, y);
+        __builtin_amdgcn_sched_barrier(0);  // a pair of values in hand at a time
+    }
+    const double b0 = swap_add16(a[0], a[2]), b1 = swap_add16(a[1], a[3]);
+    double s = fold_add<kDppRowMirror>(b0, b1, (lane & 8) != 0);
+    s += dpp_mov<kDppHalfMirror>(s);
+    s += dpp_mov<kDppXor2>(s);
+    s += dpp_mov<kDppXor1>(s);
+    return s;
+}
+
 // The largest v over the 64 lanes, in every lane.
 __device__ __forceinline__ float wave_max_v(float v) {
     v = fmaxf(v, dpp_mov<kDppXor1>(v));
