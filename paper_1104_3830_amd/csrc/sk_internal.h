@@ -77,7 +77,9 @@ struct Ctl {
     // deformed iteration on real-valued weights: p of the current iteration
     // unrounded (p is its rounding, used by the integer path)
     double preal;
+    uint32_t coop;          // outcome of the last resident launch (sk_coop.hip): kCoopOk, ...
 };
+enum : uint32_t { kCoopOk = 0, kCoopFailed = 1, kCoopBailed = 2 };
 
 // Per-instance descriptor (device memory, constant during a launch).
 struct Inst {
@@ -162,6 +164,7 @@ struct Inst {
     int32_t chk_seg, chk_nseg;
     double *chk;
     void *pot;              // the caller's potentials buffer (batches)
+    void *coop;             // exchange area of the resident iteration, or nullptr
 };
 // Doubles of one of the check's arrays of n, and of the whole scratch.
 __host__ __device__ constexpr size_t check_stride(int n) { return ((size_t)n + 31) / 32 * 32; }
@@ -312,6 +315,13 @@ hipError_t launch_mid_pair(const Inst *d_insts, const RowUnit *d_units, int nwid
 enum : int { kFinOnePass = 1, kFinStoredK = 2 };
 hipError_t launch_col_finalize(const Inst *d_insts, const FinUnit *d_units, int nunits, int grid,
                                int mode, hipStream_t st);
+// The resident iteration of one instance (index 0; sk_coop.hip): its exchange
+// area, cleared once per run, and up to `budget` iterations per launch.
+size_t coop_bytes(int n);
+hipError_t launch_coop_clear(const Inst *d_insts, int n, hipStream_t st);
+// real: real-valued log-weights (sk_coop_real.hip).
+hipError_t launch_coop(const Inst *d_insts, int n, int real, int budget, hipStream_t st);
+void launch_coop_real(const Inst *d_insts, int n, int nblk, int budget, hipStream_t st);
 // The FP64 check. Tables of units, or for one instance (null) its index and
 // the number of its units; ended: only instances that are not running.
 hipError_t launch_check_rows(const Inst *d_insts, const RowUnit *d_units, int nunits, int grid, int ended,

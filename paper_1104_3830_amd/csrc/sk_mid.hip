@@ -1,5 +1,6 @@
 // Sinkhorn iteration of instances with kSmallN < n <= kMidN in one launch per
-// iteration.
+// iteration: batches, and one instance alone where the resident iteration of
+// sk_coop.h (7.5 us at n = 1003) gave up.
 //
 // What bounds it. Such a matrix (2 MB at n = 1024) sits in the L2 caches and
 // takes about a microsecond to sweep, but an iteration of the sweeps is four

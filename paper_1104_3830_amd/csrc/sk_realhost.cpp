@@ -76,7 +76,10 @@ using namespace sk;
 
 size_t sk_real_arena_bytes(int32_t n, int64_t max_kept) {
     if (n < 1 || n > kLdsMaxN || max_kept < 0) return 0;
-    return instance_bytes(n, 1, SK_W_I16) + shared_bytes(1, &n) + real_shared_extra(n, max_kept) + 4096;
+    // up to kMidN the resident iteration's exchange area and second copies
+    const size_t coop = n > kMidN ? 0 : align_up(coop_bytes(n), 256) + align_up(sizeof(Ctl), 256) +
+                                            2 * align_up(sizeof(float) * (size_t)n, 256);
+    return instance_bytes(n, 1, SK_W_I16) + shared_bytes(1, &n) + real_shared_extra(n, max_kept) + coop + 4096;
 }
 
 sk_status sk_scale_real(sk_ctx *ctx, const float *W, int32_t n, const sk_params *params,

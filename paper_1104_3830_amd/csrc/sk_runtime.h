@@ -41,6 +41,7 @@ struct Batch {
     int nsweep_fins = 0;
     int nmid = 0, mid_wide = 0;     // instances of k_mid; units of those with n > 512 (first in h_mid)
     bool mid_fold = false;          // launch_mid_pair's fold
+    bool coop = false;              // one instance of k_mid's sizes that iterates in resident launches
     int small_class[kSmallClasses] = {};  // of the latter, those with 64 c < n <= 64 (c + 1)
     int sweep_nmax = 0;  // largest n of the former
     std::vector<Inst> h_insts;

@@ -599,6 +599,24 @@ sk_status sk::finish_tables(sk_ctx *ctx, Bump &bump, Batch &B) {
         chk_used += chk;
     }
     B.chk_end.push_back(B.count);
+    // one instance: the exchange area of the resident iteration. Its room is
+    // that of the single-pass slots in sk_arena_bytes; where the caller's
+    // arena lacks it, the instance takes a launch per iteration, with the same
+    // results.
+    B.coop = false;
+    const auto resident = [](const Inst &I) { return I.mid || (I.Wr && I.n <= kMidN && I.deform_a <= 0.0); };
+    if (B.count == 1 && resident(B.h_insts[0])) {
+        Inst &I0 = B.h_insts[0];
+        Bump b2 = bump;
+        if (I0.Wr) {
+            I0.ctl2 = b2.take<Ctl>(1);
+            I0.G2 = b2.take<int32_t>(I0.n);
+            I0.gam2 = b2.take<float>(I0.n);
+        }
+        I0.coop = b2.take<char>(coop_bytes(I0.n));
+        B.coop = I0.ctl2 && I0.G2 && I0.gam2 && I0.coop;
+        if (B.coop) bump = b2;
+    }
     // grids: row sweep stages pad8(n) columns of potentials (8 B each) in LDS
     // (above kLdsMaxN it reads them from the instance's packed buffer)
     const size_t lds = B.nmax > kLdsMaxN ? 0 : sizeof(float2) * (size_t)pad8(B.nmax);
@@ -690,6 +708,7 @@ sk_status sk::upload_batch(sk_ctx *ctx, Batch &B) {
 // Initial control blocks and the input scan (cold start or warm start).
 sk_status sk::start_batch(sk_ctx *ctx, Batch &B, const sk_params *prm, void *const *pot_in) {
     HIPCHK(ctx, launch_reset_ctl(B.d_insts, nullptr, B.count, ctx->stream));
+    if (B.coop) HIPCHK(ctx, launch_coop_clear(B.d_insts, B.h_insts[0].n, ctx->stream));
     if (prm->warm_start) {
         const bool one = B.count == 1;
         HIPCHK(ctx, launch_copy_pot(B.d_insts, one ? nullptr : B.d_fins, 0, (int)B.h_fins.size(),
@@ -806,17 +825,28 @@ sk_status sk::run_batch_i16(sk_ctx *ctx, Batch &B, const sk_params *prm, int fir
         blk = (int)std::min<int64_t>(check, std::max<int64_t>(
                                                 4, ctx->h_ctl[0].stage_iters[first_stage - 1] + 2));
     for (;;) {
-        if (swept)
+        if (swept && !B.coop)
             for (int k = 0; k < blk; ++k) {
                 sk_status s = iterate_i16(ctx, B, k > 0);
                 if (s != SK_OK) return s;
             }
-        sk_status s = mid ? iterate_mid(ctx, B, blk) : SK_OK;
+        sk_status s = SK_OK;
+        if (B.coop)
+            HIPCHK(ctx, PROF(ctx, KID_MID, launch_coop(B.d_insts, B.nmax, B.h_insts[0].Wr != nullptr, kSmallBudget,
+                                                       ctx->stream)));
+        else if (mid)
+            s = iterate_mid(ctx, B, blk);
         if (s == SK_OK) s = iterate_small(ctx, B, kSmallBudget);
         if (s != SK_OK) return s;
         // every running instance has moved on by its block
-        launched += swept || mid ? blk : kSmallBudget;
+        launched += (swept || mid) && !B.coop ? blk : kSmallBudget;
         if ((s = read_ctl(ctx, B)) != SK_OK) return s;
+        // its workgroups were not all resident, or a column needs the exact
+        // max shift: the rest of the run takes a launch per iteration
+        if (B.coop && ctx->h_ctl[0].coop != kCoopOk) {
+            B.coop = false;
+            launched = 0;
+        }
         bool running = false, tail = true;
         swept = mid = false;
         for (int k = 0; k < B.count; ++k) {

@@ -122,3 +122,32 @@ def test_empty_row_or_column(ctx, n):
         with pytest.raises(sk.SkError) as e:
             ctx.scale(dev(W), sk.make_params([1, 2], tol=1e-6, max_iters=50))
         assert e.value.status == sk.SK_ENOSUPPORT
+
+
+@pytest.mark.parametrize("n", [257, 300, 512, 513, 800, 1023, 1024])
+@pytest.mark.parametrize("tol,cap", [(0.0, 11), (1e-4, 400)])
+def test_resident_and_launched_iterations_agree_bitwise(ctx, n, tol, cap):
+    """One instance iterates in a resident launch, a batch with a launch per
+    iteration; few instances take the column step in the same launch, many in
+    one of its own: the same bits, iterations and residuals either way."""
+    W = skgen.uniform_weights(n, 0, 50, seed=n)
+    W[n // 3, n // 5:] = sk.SENTINEL
+    prm = sk.make_params([1, 2, 3], tol=tol, max_iters=cap)
+    Wd = dev(W)
+    one = ctx.scale(Wd, prm)
+    few = ctx.scale_batch([Wd, dev(skgen.uniform_weights(280, 0, 50, seed=1))], prm)[0]
+    many = ctx.scale_batch([Wd] + [dev(skgen.uniform_weights(1000 - k, 0, 50, seed=k)) for k in range(9)], prm)[0]
+    for other in (few, many):
+        assert one.report["iters_stage"] == other.report["iters_stage"]
+        assert one.report["residual_fp32"] == other.report["residual_fp32"]
+        assert torch.equal(one.potentials, other.potentials)
+
+
+def test_resident_run_longer_than_a_launch(ctx):
+    """More iterations than one resident launch takes."""
+    W = dev(skgen.uniform_weights(270, 0, 100, seed=4))
+    prm = sk.make_params([2], tol=0.0, max_iters=4200)
+    one = ctx.scale(W, prm)
+    assert one.report["iters_total"] == 4200
+    two = ctx.scale_batch([W, W], prm)
+    assert torch.equal(one.potentials, two[0].potentials) and torch.equal(one.potentials, two[1].potentials)
