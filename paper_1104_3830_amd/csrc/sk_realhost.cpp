@@ -157,6 +157,9 @@ sk_status sk_solve_real(sk_ctx *ctx, const float *W, int32_t n, const sk_params 
         std::vector<int32_t> perm;
         sk_report rep{};
     } best;
+    // where the exact solve starts: the first from the scaling's log v, the
+    // following ones from the optimum of the one before
+    MatchStart start;
     bool reached = false;
     int evaluated = 0;
     auto evaluate = [&](const Ctl &c, bool last, bool &stop) -> sk_status {
@@ -177,6 +180,17 @@ sk_status sk_solve_real(sk_ctx *ctx, const float *W, int32_t n, const sk_params 
         double wB = 0.0;
         bool feasible = false;
         int64_t nnz = 0;
+        const double pe = (params->deform_a > 0.0 ? c.preal : (double)c.p) * pscale;
+        std::vector<int32_t> gh;
+        std::vector<float> gamh;
+        if (start.v.empty()) {
+            gh.resize((size_t)n);
+            gamh.resize((size_t)n);
+            HIPCHK(ctx, hipMemcpyAsync(gh.data(), B.h_insts[0].G, sizeof(int32_t) * (size_t)n,
+                                       hipMemcpyDeviceToHost, ctx->stream));
+            HIPCHK(ctx, hipMemcpyAsync(gamh.data(), B.h_insts[0].gam, sizeof(float) * (size_t)n,
+                                       hipMemcpyDeviceToHost, ctx->stream));
+        }
         // a B with no perfect matching at the last p: lower t tenfold, at most three times
         for (int tries = 0;; ++tries) {
             const CheckCounts cc{std::log(t), B.d_counts, d_hint};
@@ -188,8 +202,7 @@ sk_status sk_solve_real(sk_ctx *ctx, const float *W, int32_t n, const sk_params 
             HIPCHK(ctx, hipMemcpyAsync(ctx->h_nnz, B.d_nnz, sizeof(int64_t), hipMemcpyDeviceToHost,
                                        ctx->stream));
             HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
-            report_from_check(ctx->h_checkout, (params->deform_a > 0.0 ? c.preal : (double)c.p) * pscale, &rep,
-                              n, wref);
+            report_from_check(ctx->h_checkout, pe, &rep, n, wref);
             nnz = ctx->h_nnz[0];
             Bump tmp = rest;
             int32_t *d_col = tmp.take<int32_t>((size_t)std::max<int64_t>(nnz, 1));
@@ -213,7 +226,14 @@ sk_status sk_solve_real(sk_ctx *ctx, const float *W, int32_t n, const sk_params 
             HIPCHK(ctx, hipMemcpyAsync(hint.data(), d_hint, sizeof(int32_t) * (size_t)n, hipMemcpyDeviceToHost,
                                        ctx->stream));
             HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
-            s2 = solve_real_impl(n, rp.data(), colh.data(), wh.data(), hint.data(), pm.data(), &wB);
+            if (start.v.empty()) {
+                start.v.resize((size_t)n);
+                for (int j = 0; j < n; ++j) {
+                    const double v = ((double)gh[j] + (double)gamh[j]) / pe;
+                    start.v[j] = std::isfinite(v) ? v : 0.0;
+                }
+            }
+            s2 = solve_real_impl(n, rp.data(), colh.data(), wh.data(), hint.data(), &start, pm.data(), &wB);
             if (s2 == SK_OK) {
                 feasible = true;
                 break;
