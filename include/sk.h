@@ -383,7 +383,7 @@ sk_status sk_set_tile_table(const int32_t *n_max, const int32_t *seg_rows, int32
 /* Kernel timing (measurement aid, off by default). While enabled, the
  * context's kernels are timed with HIP events on its stream: the two sweeps
  * of an iteration share the event between them, the short per-iteration
- * finalise and end-of-iteration launches are not timed, and the other
+ * finalise launches are not timed, and the other
  * kernels are bracketed one by one; durations accumulate per kernel name
  * (launches that only detected a stage end or came after every instance
  * finished are counted under "<name>:detect" and "<name>:idle") until the

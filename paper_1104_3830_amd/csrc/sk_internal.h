@@ -59,7 +59,7 @@ enum : uint32_t { ERR_EMPTY_ROW = 1u, ERR_EMPTY_COL = 2u, ERR_RANGE = 4u, ERR_NE
 // Per-instance control block, device memory. Written by the kernels only at
 // the places documented on each field; read by the host between launches.
 struct Ctl {
-    uint32_t res_bits;      // max_i |r_i - 1| of the current iterate (float bits), from the finalise
+    uint32_t arrived;       // workgroups of the running finalise that are done (low half), that flagged (high)
     uint32_t rescue_cnt;    // columns whose sum left the safe range in the last column sweep
     uint32_t err;           // ERR_* flags
     uint32_t sent;          // 1: W holds the sentinel (set by the input scan)
@@ -143,7 +143,6 @@ struct Inst {
     // within a few p times the weight range.
     const float *Wr;
     float wref;
-    int32_t sweep_idx;
     // p of the current stage is ctl->p * pscale: 1 for int16 W; with the
     // prescaling of Section 4.1.1, 1 / (w_max - w_min) when that exceeds 1
     double pscale;
@@ -298,9 +297,6 @@ hipError_t launch_nt_product(const Inst *d_insts, const RowUnit *d_rows, int nro
 hipError_t launch_nt_step(const Inst *d_insts, NtCtl *nt, NtVec vec, int n, hipStream_t st);
 hipError_t launch_nt_fold(const Inst *d_insts, const NtCtl *nt, NtVec vec, int n, int last,
                           hipStream_t st);
-// The instances insts[0 .. count).sweep_idx.
-hipError_t launch_iter_end(const Inst *d_insts, int count, hipStream_t st,
-                           hipEvent_t stop = nullptr);
 // Up to `budget` iterations of the small instances; counts[c]: how many have
 // 64 c < n <= 64 (c + 1). The list of small_idx holds the largest class first.
 hipError_t launch_small(const Inst *d_insts, const int *counts, int budget, hipStream_t st);
@@ -313,8 +309,10 @@ hipError_t set_small_attributes();
 hipError_t launch_mid_pair(const Inst *d_insts, const RowUnit *d_units, int nwide, int nnarrow, int ninst, int fold,
                            hipStream_t st);
 enum : int { kFinOnePass = 1, kFinStoredK = 2 };
-hipError_t launch_col_finalize(const Inst *d_insts, const FinUnit *d_units, int nunits, int grid,
-                               int mode, hipStream_t st);
+// The column step, and the end of each instance's iteration. d_units null:
+// instance 0 alone.
+hipError_t launch_finalize(const Inst *d_insts, const FinUnit *d_units, int nunits, int mode, hipStream_t st,
+                           hipEvent_t stop = nullptr);
 // The resident iteration of one instance (index 0; sk_coop.hip): its exchange
 // area, cleared once per run, and up to `budget` iterations per launch.
 size_t coop_bytes(int n);

@@ -141,11 +141,6 @@ __device__ __forceinline__ bool deform_settled(const Inst &I, const Ctl *ctl) {
     return deform_p(I, ctl->iter) == I.ladder[I.n_p - 1];
 }
 
-__device__ __forceinline__ bool stage_converged(const Inst &I, const Ctl *ctl) {
-    const float res = __uint_as_float(ctl->res_bits);
-    return ctl->iter >= 1 && res < I.tol && deform_settled(I, ctl);
-}
-
 // Row data of the column sweep: b = 4 (F_i - kTabLo), r = exp(phi_i).
 struct alignas(8) RowPot {
     int b;
@@ -368,131 +363,16 @@ __global__ __launch_bounds__(kColWaves * kWave, EARLY ? 1 : 6) void k_col_sweep(
     }
 }
 
-// ---------------------------------------------------------------- column step (finalise)
-// Workgroup = 64 columns of one instance, four threads per column. It reduces
-// the residual slots of the current iterate (stopping test; group 0 publishes
-// the value for the end-of-iteration kernel), and unless the stage has
-// converged adds each column's fixed slots in slot order and applies the
-// column step (eq. dad3):
-//   log-domain sweeps:   slots hold sum_i exp(p w_ij + log u_i + G_j):  gam_j <- -log C_j
-//   log-domain 1 pass:   slots hold the column sum of the iterate:       gam_j <- gam_j - log C_j
-//   stored K sweeps:     slots hold sum_i K_ij a_i:                      b_j <- 1 / C_j
-//   stored K 1 pass:     slots hold b_j sum_i K_ij a_i:                  b_j <- b_j / C_j
-// A log-domain column whose sum leaves [2^-64, 2^64] is queued for the exact
-// recompute of the end-of-iteration kernel.
-// Column slots a thread holds in registers (4 threads per column): up to
-// 4 * kFinPre slots (the sweeps' row segments) are requested at the unit's
-// start, before the controller is read, so that the unit costs one memory
-// round trip; more slots (the single pass) are read in the loop.
-constexpr int kFinPre = 8;
-
-__global__ __launch_bounds__(256) void k_col_finalize(const Inst *__restrict__ insts,
-                                                      const FinUnit *__restrict__ units, int nunits,
-                                                      int mode) {
-    __shared__ float part[4][kFinCols];
-    __shared__ float rmax[4], dmax[4];
-    const int t = threadIdx.x, lane = t % kWave, wave = t / kWave;
-    const bool kpath = (mode & kFinStoredK) != 0;   // slots written by the stored-K kernels
-    const bool onepass = (mode & kFinOnePass) != 0; // slots written by the single-pass kernel
-    int u0, u1;
-    unit_range(nunits, u0, u1);
-    for (int u = u0; u < u1; ++u) {
-        const FinUnit un = units[u];
-        const Inst &I = insts[un.inst];
-        Ctl *ctl = I.ctl;
-        const int n = I.n;
-        const int c = t & (kFinCols - 1), g = t / kFinCols;
-        const int j = un.group * kFinCols + c;
-        const int ns = I.ncolslots;
-        const bool pre = ns <= 4 * kFinPre;
-        float pv[kFinPre];
-        if (pre && j < n) {
-#pragma unroll
-            for (int k = 0; k < kFinPre; ++k) {
-                const int q = g + 4 * k;
-                pv[k] = q < ns ? I.colpart[(int64_t)q * n + j] : 0.f;
-            }
-        }
-        // residual (and drift) of this iteration's row step: one slot per
-        // workgroup of the single pass and of the stored-K row sweep, per
-        // row segment of the log-domain sweeps
-        const int nres = onepass ? I.fused_grid : (kpath ? I.kres_slots : I.nseg);
-        float m = 0.f, d = 0.f;
-        for (int q = t; q < nres; q += 256) {
-            m = fmaxf(m, I.res_slots[q]);
-            if (kpath) d = fmaxf(d, I.drift_slots[q]);
-        }
-        if (ctl->state != ST_RUNNING) continue;
-        if (kpath && ctl->need_absorb) continue;
-        m = wave_max(m);
-        d = wave_max(d);
-        __syncthreads();  // the previous unit's readers of rmax, dmax and part are done
-        if (lane == 0) {
-            rmax[wave] = m;
-            dmax[wave] = d;
-        }
-        __syncthreads();
-        const float res = fmaxf(fmaxf(rmax[0], rmax[1]), fmaxf(rmax[2], rmax[3]));
-        const float dm = fmaxf(fmaxf(dmax[0], dmax[1]), fmaxf(dmax[2], dmax[3]));
-        const bool conv = ctl->iter >= 1 && res < I.tol && deform_settled(I, ctl);
-        if (un.group == 0 && t == 0) {
-            ctl->res_bits = __float_as_uint(res);
-            if (kpath && dm > 0.f) atomicMax(&ctl->drift_bits, __float_as_uint(dm));
-        }
-        if (conv) continue;
-        // each thread adds the slots g, g + 4, ... of its column, alternately
-        // into two sums (fixed order)
-        float s0 = 0.f, s1 = 0.f;
-        if (j < n) {
-            if (pre) {
-#pragma unroll
-                for (int k = 0; k < kFinPre; ++k) {
-                    if (g + 4 * k >= ns) break;
-                    if (k & 1) s1 += pv[k];
-                    else s0 += pv[k];
-                }
-            } else {
-                int q = g;
-                for (; q + 4 < ns; q += 8) {
-                    s0 += I.colpart[(int64_t)q * n + j];
-                    s1 += I.colpart[(int64_t)(q + 4) * n + j];
-                }
-                for (; q < ns; q += 4) s0 += I.colpart[(int64_t)q * n + j];
-            }
-        }
-        part[g][c] = s0 + s1;
-        __syncthreads();
-        float drift = 0.f;
-        if (g == 0 && j < n) {
-            const float C = (part[0][c] + part[1][c]) + (part[2][c] + part[3][c]);
-            if (!kpath) {
-                if (C >= kSafeLo && C <= kSafeHi) {
-                    const float gn = (onepass ? I.gam[j] : 0.f) - lg2(C) * kLn2;
-                    const float k = rintf(gn);
-                    I.G[j] += (int)k;
-                    I.gam[j] = gn - k;
-                } else {
-                    const unsigned slot = atomicAdd(&ctl->rescue_cnt, 1u);
-                    I.rescue[slot] = (uint32_t)j;
-                }
-            } else {
-                const float Cc = fminf(fmaxf(C, kSafeLo), kSafeHi);
-                const float bn = fminf(fmaxf((onepass ? I.b[j] : 1.f) / Cc, kSafeLo), kSafeHi);
-                I.b[j] = bn;
-                drift = fabsf(lg2(bn));
-            }
-        }
-        if (kpath) {
-            drift = wave_max(drift);
-            if ((t % kWave) == 0 && drift > 0.f) atomicMax(&ctl->drift_bits, __float_as_uint(drift));
-        }
-    }
-}
-
 // ---------------------------------------------------------------- end of iteration
-// One workgroup per instance: exact recompute of flagged columns, commit of
-// the iteration, stopping test, and the continuation to the next p with
-// p^-1 log u and p^-1 log v held fixed (in FP64).
+// Exact recompute of flagged columns, commit of the iteration, stopping test,
+// and the continuation to the next p with p^-1 log u and p^-1 log v held fixed
+// (in FP64), by the workgroup of the finalise that ends last (kFinThreads; the
+// FP64 rescaling of all potentials at a stage change is spread over them).
+constexpr int kFinWaves = 8;
+constexpr int kFinThreads = kFinWaves * kWave;
+static_assert(kMaxN / kFinCols < 0x10000 && kRowResSlots <= kFinThreads, "");
+static_assert(kFinCols == kWave, "a wave of the finalise owns a slot's columns");
+
 __device__ void stage_advance(const Inst &I, Ctl *ctl, int par) {
     const int n = I.n;
     const int s = ctl->stage;
@@ -540,27 +420,32 @@ __device__ void end_stage(const Inst &I, Ctl *ctl, int par) {
     }
 }
 
-// One workgroup of kIterEndThreads per instance (the FP64 rescaling of all
-// potentials at a stage change is spread over all of them).
-constexpr int kIterEndThreads = 1024;
+// A flagged column's sum has kEndLanes fixed partials, whatever the workgroup.
+constexpr int kEndLanes = 1024;
+struct IterEndLds {
+    int redi[kFinThreads];
+    float red[kEndLanes];
+    double redd[kFinThreads];
+    float tab[kTabN];
+};
 
-__global__ __launch_bounds__(kIterEndThreads) void k_iter_end(const Inst *__restrict__ insts) {
-    __shared__ int redi[kIterEndThreads];
-    __shared__ float red[kIterEndThreads];
-    __shared__ float tab[kTabN];
-    const Inst &I = insts[insts[blockIdx.x].sweep_idx];
-    Ctl *ctl = I.ctl;
-    if (ctl->state != ST_RUNNING) return;
+__device__ __forceinline__ unsigned rescue_count(Ctl *ctl) {
+    return __hip_atomic_load(&ctl->rescue_cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// res: max |r_i - 1| of the iteration, conv: the stage ends with it. What
+// other workgroups of this launch wrote and this reads has been fenced.
+__device__ void iteration_end(const Inst &I, Ctl *ctl, float res, bool conv, IterEndLds &L) {
+    int *redi = L.redi;
+    float *red = L.red, *tab = L.tab;
     const int n = I.n;
-    const bool conv = stage_converged(I, ctl);
     const int iter = ctl->iter;
     const int npar = (iter + 1) & 1;
     const int p4 = 4 * ctl->p;
-    unsigned nres = conv ? 0u : ctl->rescue_cnt;
+    unsigned nres = conv ? 0u : rescue_count(ctl);
     if (I.Wr) {
         // real-valued log-weights: the same recompute with FP64 exponents
-        __shared__ double redd[kIterEndThreads];
-        for (unsigned q = 0; q < nres; ++q) real_rescue_column(I, ctl, (int)I.rescue[q], npar, redd);
+        for (unsigned q = 0; q < nres; ++q) real_rescue_column(I, ctl, (int)I.rescue[q], npar, L.redd);
         nres = 0u;
     }
     if (nres > 0u) fill_exp_table(tab);
@@ -579,29 +464,29 @@ __global__ __launch_bounds__(kIterEndThreads) void k_iter_end(const Inst *__rest
         __syncthreads();
         redi[threadIdx.x] = m;
         __syncthreads();
-        for (int o = kIterEndThreads / 2; o > 0; o >>= 1) {
+        for (int o = kFinThreads / 2; o > 0; o >>= 1) {
             if ((int)threadIdx.x < o) redi[threadIdx.x] = max(redi[threadIdx.x], redi[threadIdx.x + o]);
             __syncthreads();
         }
         const int m4 = redi[0];
         const int M = m4 >> 2;  // exact: m4 is a multiple of 4 (unused when m4 == INT_MIN)
-        float sacc = 0.f;
-        if (m4 != INT_MIN) {
-            for (int r = threadIdx.x; r < n; r += blockDim.x) {
+        for (int v = threadIdx.x; v < kEndLanes; v += kFinThreads) {
+            float sacc = 0.f;
+            for (int r = v; r < n && m4 != INT_MIN; r += kEndLanes) {
                 const int w = (int)I.W[(int64_t)r * I.pitch + j];
                 if (w == SK_SENTINEL) continue;
                 const float e = tab_at(tab, tab_off(p4, w, A, 4 * (I.F[npar][r] - M - kTabLo)));
                 sacc = fmaf(e, ex2(I.phi[npar][r] * kLog2e), sacc);
             }
+            red[v] = sacc;
         }
-        red[threadIdx.x] = sacc;
         __syncthreads();
         if (threadIdx.x == 0) {
             if (m4 == INT_MIN) {
                 atomicOr(&ctl->err, ERR_EMPTY_COL);
             } else {
                 float S = 0.f;
-                for (int t = 0; t < (int)blockDim.x; ++t) S += red[t];
+                for (int t = 0; t < kEndLanes; ++t) S += red[t];
                 // log v_j <- G_j - M - log S
                 const float gn = -lg2(S) * kLn2;
                 const float k = rintf(gn);
@@ -615,22 +500,19 @@ __global__ __launch_bounds__(kIterEndThreads) void k_iter_end(const Inst *__rest
     __syncthreads();
     if (threadIdx.x == 0) {
         ctl->rescue_cnt = 0u;
+        ctl->arrived = 0u;
         if (ctl->err & (ERR_EMPTY_ROW | ERR_EMPTY_COL)) ctl->state = ST_ERROR;
     }
     __syncthreads();
     if (ctl->state != ST_RUNNING) return;
     if (conv) {
-        if (threadIdx.x == 0) {
-            ctl->last_res = __uint_as_float(ctl->res_bits);
-            ctl->res_bits = 0u;
-        }
+        if (threadIdx.x == 0) ctl->last_res = res;
         end_stage(I, ctl, iter & 1);
         return;
     }
     // commit: the new row potentials are in buffer npar, i.e. (iter+1) & 1
     if (threadIdx.x == 0) {
-        if (iter >= 1) ctl->last_res = __uint_as_float(ctl->res_bits);
-        ctl->res_bits = 0u;
+        if (iter >= 1) ctl->last_res = res;
         ctl->iter = iter + 1;
         ctl->iters_total += 1;
         ctl->stage_iters[ctl->stage] += 1;
@@ -643,6 +525,149 @@ __global__ __launch_bounds__(kIterEndThreads) void k_iter_end(const Inst *__rest
         // deformed iteration: the next iteration's p, potentials unscaled
         ctl->p = deform_p(I, iter + 2);
         ctl->preal = deform_p_real(I, iter + 2);
+    }
+}
+
+// ---------------------------------------------------------------- column step (finalise)
+// Workgroup = 64 columns of one instance, a wave per 8th slot. It reduces the
+// residual slots of the current iterate (stopping test), and unless the stage
+// has converged adds each column's fixed slots in a fixed order and applies
+// the column step (eq. dad3):
+//   log-domain sweeps:   slots hold sum_i exp(p w_ij + log u_i + G_j):  gam_j <- -log C_j
+//   log-domain 1 pass:   slots hold the column sum of the iterate:       gam_j <- gam_j - log C_j
+//   stored K sweeps:     slots hold sum_i K_ij a_i:                      b_j <- 1 / C_j
+//   stored K 1 pass:     slots hold b_j sum_i K_ij a_i:                  b_j <- b_j / C_j
+// A log-domain column whose sum leaves [2^-64, 2^64] is queued for the exact
+// recompute at the end of the iteration, which the instance's last workgroup
+// to get there takes (nothing of the iteration's state changes before).
+//
+// What bounds it: memory latency, a few dependent round trips. A thread
+// requests its slots (at most kFinSlots) at the start, before the controller
+// is read; the last workgroup only writes, unless the stage ends or columns
+// were flagged. Against a finalise of four threads per column and a launch of
+// one workgroup for the end of the iteration: 8.5 -> 6.1 us at n = 4096 (32
+// slots), 16.9 -> 7.3 at n = 8192 (256 slots), 9.9 -> 9.1 at n = 16384 (32
+// slots; 256 workgroups count on one word). With a fence in every workgroup
+// it was no better than the two launches.
+constexpr int kFinSlots = (kFusedSlots + kFinWaves - 1) / kFinWaves;  // 32
+
+__global__ __launch_bounds__(kFinThreads) void k_col_finalize(const Inst *__restrict__ insts,
+                                                              const FinUnit *__restrict__ units, int mode) {
+    __shared__ float part[kFinWaves][kFinCols];
+    __shared__ float rmax[kFinWaves], dmax[kFinWaves];
+    __shared__ IterEndLds L;
+    __shared__ unsigned arrived;
+    const int t = threadIdx.x, lane = t % kWave, wave = t / kWave;
+    const bool kpath = (mode & kFinStoredK) != 0;   // slots written by the stored-K kernels
+    const bool onepass = (mode & kFinOnePass) != 0; // slots written by the single-pass kernel
+    FinUnit un{0, (int)blockIdx.x};
+    if (units) un = units[blockIdx.x];
+    const Inst &I = insts[un.inst];
+    Ctl *ctl = I.ctl;
+    const int n = I.n;
+    const int j = un.group * kFinCols + lane;
+    const int ns = I.ncolslots;
+    float pv[kFinSlots];
+#pragma unroll
+    for (int k = 0; k < kFinSlots; ++k) {
+        const int q = wave + kFinWaves * k;
+        pv[k] = q < ns && j < n ? I.colpart[(int64_t)q * n + j] : 0.f;
+    }
+    // residual (and drift) of this iteration's row step: one slot per
+    // workgroup of the single pass and of the stored-K row sweep, per
+    // row segment of the log-domain sweeps
+    const int nres = onepass ? I.fused_grid : (kpath ? I.kres_slots : I.nseg);
+    float m = 0.f, d = 0.f;
+    for (int q = t; q < nres; q += kFinThreads) {
+        m = fmaxf(m, I.res_slots[q]);
+        if (kpath) d = fmaxf(d, I.drift_slots[q]);
+    }
+    const int state = ctl->state, iter = ctl->iter, stage = ctl->stage;
+    const unsigned err = ctl->err, absorb = ctl->need_absorb;
+    const float gam0 = onepass && !kpath && j < n ? I.gam[j] : 0.f;
+    const int G0 = !kpath && j < n ? I.G[j] : 0;
+    if (state != ST_RUNNING) return;
+    if (kpath && absorb) return;
+    // the thread's slots in order
+    float sum = pv[0];
+#pragma unroll
+    for (int k = 1; k < kFinSlots; ++k) sum += pv[k];
+    // more row segments than that: a tile table of the caller's
+    for (int q = wave + kFinWaves * kFinSlots; q < ns && j < n; q += kFinWaves)
+        sum += I.colpart[(int64_t)q * n + j];
+    part[wave][lane] = sum;
+    m = wave_max(m);
+    d = wave_max(d);
+    if (lane == 0) {
+        rmax[wave] = m;
+        dmax[wave] = d;
+    }
+    __syncthreads();
+    float res = rmax[lane % kFinWaves], dm = dmax[lane % kFinWaves];
+    res = wave_max(res);
+    dm = wave_max(dm);
+    const bool conv = iter >= 1 && res < I.tol && deform_settled(I, ctl);
+    if (kpath && un.group == 0 && t == 0 && dm > 0.f) atomicMax(&ctl->drift_bits, __float_as_uint(dm));
+    bool flagged = false;
+    if (wave == 0 && !conv) {
+        float drift = 0.f;
+        if (j < n) {
+            float h[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) h[k] = part[k][lane] + part[k + 4][lane];
+            const float C = (h[0] + h[1]) + (h[2] + h[3]);
+            if (!kpath) {
+                if (C >= kSafeLo && C <= kSafeHi) {
+                    const float gn = gam0 - lg2(C) * kLn2;
+                    const float k = rintf(gn);
+                    I.G[j] = G0 + (int)k;
+                    I.gam[j] = gn - k;
+                } else {
+                    const unsigned slot = atomicAdd(&ctl->rescue_cnt, 1u);
+                    I.rescue[slot] = (uint32_t)j;
+                    flagged = true;
+                }
+            } else {
+                const float Cc = fminf(fmaxf(C, kSafeLo), kSafeHi);
+                const float bn = fminf(fmaxf((onepass ? I.b[j] : 1.f) / Cc, kSafeLo), kSafeHi);
+                I.b[j] = bn;
+                drift = fabsf(lg2(bn));
+            }
+        }
+        if (kpath) {
+            drift = wave_max(drift);
+            if (lane == 0 && drift > 0.f) atomicMax(&ctl->drift_bits, __float_as_uint(drift));
+        }
+    }
+    // The last workgroup reads what others wrote in this launch in two cases
+    // only: a list of flagged columns, and potentials that move to the next p
+    // because the stage is capped. Wave 0 alone wrote, so its own fence before
+    // its count is enough; a fence on every iteration costs 3 us.
+    const bool capped = !conv && (int64_t)iter + 1 >= I.max_iters;
+    const unsigned groups = (unsigned)((n + kFinCols - 1) / kFinCols);
+    if (wave == 0) {
+        const bool any = __any(flagged);
+        if (capped || any) __threadfence();
+        // the count of workgroups done, and above it of those that flagged
+        if (lane == 0)
+            arrived = __hip_atomic_fetch_add(&ctl->arrived, any ? 0x10001u : 1u, __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT) + (any ? 0x10000u : 0u);
+    }
+    __syncthreads();
+    if ((arrived & 0xffffu) != groups - 1u) return;
+    if (conv || capped || arrived > 0xffffu || err || I.deform_a > 0.0) {
+        __threadfence();
+        iteration_end(I, ctl, res, conv, L);
+        return;
+    }
+    // an ordinary iteration: writes alone, nothing to wait for
+    if (t < kRowResSlots) I.rowres[t * kRowResStride] = 0u;
+    if (t == 0) {
+        ctl->arrived = 0u;
+        if (iter >= 1) ctl->last_res = res;
+        ctl->iter = iter + 1;
+        atomicAdd((unsigned long long *)&ctl->iters_total, 1ull);
+        atomicAdd((unsigned long long *)&ctl->stage_iters[stage], 1ull);
     }
 }
 
@@ -2146,9 +2171,10 @@ hipError_t launch_col_sweep(const Inst *d_insts, const ColUnit *d_units, int nun
     }
     return hipGetLastError();
 }
-hipError_t launch_col_finalize(const Inst *d_insts, const FinUnit *d_units, int nunits, int grid,
-                               int mode, hipStream_t st) {
-    hipLaunchKernelGGL(k_col_finalize, dim3(grid), dim3(256), 0, st, d_insts, d_units, nunits, mode);
+hipError_t launch_finalize(const Inst *d_insts, const FinUnit *d_units, int nunits, int mode, hipStream_t st,
+                           hipEvent_t stop) {
+    if (nunits < 1) return hipSuccess;
+    launch_stamped(k_col_finalize, dim3(nunits), dim3(kFinThreads), 0, st, stop, d_insts, d_units, mode);
     return hipGetLastError();
 }
 hipError_t launch_nt_product(const Inst *d_insts, const RowUnit *d_rows, int nrows, int row_grid,
@@ -2179,10 +2205,6 @@ hipError_t launch_nt_fold(const Inst *d_insts, const NtCtl *nt, NtVec vec, int n
                           hipStream_t st) {
     hipLaunchKernelGGL(k_nt_fold, dim3((n + 255) / 256), dim3(256), 0, st, d_insts, nt + 1, vec.x,
                        last);
-    return hipGetLastError();
-}
-hipError_t launch_iter_end(const Inst *d_insts, int count, hipStream_t st, hipEvent_t stop) {
-    launch_stamped(k_iter_end, dim3(count), dim3(kIterEndThreads), 0, st, stop, d_insts);
     return hipGetLastError();
 }
 hipError_t launch_check_rows(const Inst *d_insts, const RowUnit *d_units, int nunits, int grid, int ended,

@@ -726,10 +726,9 @@ sk_status run_single_k(sk_ctx *ctx, Batch &B, const sk_params *prm, const StageH
                 pf.add(KID_ROW_K, s0, s1);
                 pf.add(KID_COL_K, s1, s2);
             }
-            // finalise and end of iteration: short, not stamped
-            KCHK(launch_col_finalize(B.d_insts, B.d_fins, B.nsweep_fins, B.fin_grid,
-                                     kFinStoredK | (I0.fused ? kFinOnePass : 0), ctx->stream));
-            KCHK(launch_iter_end(B.d_insts, B.nsweep, ctx->stream));
+            // finalise: short, not stamped
+            KCHK(launch_finalize(B.d_insts, nullptr, B.nsweep_fins,
+                                 kFinStoredK | (I0.fused ? kFinOnePass : 0), ctx->stream));
         }
         if (ctx->prof.on) {
             if ((st = read_ctl(ctx, B)) != SK_OK) return st;

@@ -64,7 +64,7 @@ struct Batch {
     int64_t *d_counts = nullptr;
     size_t row_lds = 0;
     size_t row_lds_k = 0;
-    int row_grid = 1, col_grid = 1, row_grid_k = 1, fin_grid = 1;
+    int row_grid = 1, col_grid = 1, row_grid_k = 1;
 };
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
@@ -84,7 +84,7 @@ struct Bump {
 };
 struct Server;
 
-// Timed launch classes (the short finalise and end-of-iteration launches of
+// Timed launch classes (the short finalise launches of
 // an iteration are not timed). *_DETECT: a launch that only detected the end
 // of a stage; *_IDLE: a launch after every instance finished.
 enum KernelId {
@@ -138,7 +138,7 @@ struct Profiler {
     ~Profiler();
     int cur_id = -1;
     int cur_start = -1;
-    int iter_end_stamp = -1;  // end stamp of the last end-of-iteration launch
+    int iter_end_stamp = -1;  // end stamp of the last iteration's last launch
 };
 
 }  // namespace sk
@@ -201,7 +201,7 @@ sk_status plan_batch(sk_ctx *ctx, Bump &bump, int count, const int16_t *const *W
 sk_status upload_batch(sk_ctx *ctx, Batch &B);
 sk_status start_batch(sk_ctx *ctx, Batch &B, const sk_params *prm, void *const *pot_in);
 sk_status read_ctl(sk_ctx *ctx, Batch &B);
-// chained: the previous launch on the stream is the end-of-iteration launch
+// chained: the previous launch on the stream is the last one
 // of the previous call (timing then starts from that launch's end stamp).
 sk_status iterate_i16(sk_ctx *ctx, Batch &B, bool chained = false);
 // One launch of up to `budget` iterations of the batch's small instances.

@@ -503,7 +503,7 @@ sk_status sk::finish_tables(sk_ctx *ctx, Bump &bump, Batch &B) {
         for (int s = 0; s < I.nseg; ++s)
             for (int tt = 0; tt < I.ntiles; ++tt) B.h_cols.push_back(ColUnit{k, tt, s, 0});
         B.sweep_nmax = std::max(B.sweep_nmax, I.n);
-        B.h_insts[B.nsweep++].sweep_idx = k;
+        B.nsweep += 1;
     }
     for (int k = 0; k < B.count; ++k)
         if (B.h_insts[k].small || B.h_insts[k].mid) B.order.push_back(k);
@@ -664,7 +664,6 @@ sk_status sk::finish_tables(sk_ctx *ctx, Bump &bump, Batch &B) {
         if (!B.d_row_bounds) return fail(ctx, SK_ENOMEM, "arena too small for the batch tables");
     }
     B.col_grid = (int)std::max<size_t>(1, std::min<size_t>(B.h_cols.size(), (size_t)ctx->num_cus * 8));
-    B.fin_grid = (int)std::max<size_t>(1, std::min<size_t>(B.nsweep_fins, (size_t)ctx->num_cus * 4));
     return SK_OK;
 }
 
@@ -743,16 +742,13 @@ sk_status sk::iterate_i16(sk_ctx *ctx, Batch &B, bool chained) {
         const Inst &I = B.h_insts[0];
         HIPCHK(ctx, PROF(ctx, KID_FUSED, launch_fused(B.d_insts, 0, I.n, I.fused_grid, SK_W_I16,
                                                       I.nt, ctx->stream)));
-        HIPCHK(ctx, launch_col_finalize(B.d_insts, B.d_fins, B.nsweep_fins, B.fin_grid,
-                                        kFinOnePass, ctx->stream));
-        HIPCHK(ctx, launch_iter_end(B.d_insts, B.nsweep, ctx->stream));
+        HIPCHK(ctx, launch_finalize(B.d_insts, B.count == 1 ? nullptr : B.d_fins, B.nsweep_fins, kFinOnePass, ctx->stream));
         pf.iter_end_stamp = -1;
         return SK_OK;
     }
-    // timed: the two sweeps. Each sweep and the end-of-iteration launch
-    // record their own end stamps; the row sweep is timed from the previous
-    // iteration's end stamp when this call follows it directly, else from a
-    // marker. The short finalise launch between is not stamped.
+    // timed: the two sweeps. Each launch records its own end stamp; the row
+    // sweep is timed from the previous iteration's end stamp when this call
+    // follows it directly, else from a marker.
     const Inst &I0 = B.h_insts[0];
     // n > kLdsMaxN (one instance): the row sweep reads the column entries
     // packed here (timed with it)
@@ -777,9 +773,8 @@ sk_status sk::iterate_i16(sk_ctx *ctx, Batch &B, bool chained) {
                                      B.sweep_nmax <= kShortRowN, ctx->stream, e2));
     pf.add(KID_ROW, s0, s1);
     pf.add(KID_COL, s1, s2);
-    HIPCHK(ctx, launch_col_finalize(B.d_insts, B.d_fins, B.nsweep_fins, B.fin_grid, 0, ctx->stream));
     hipEvent_t e3 = pf.kernel_stamp(&s3);
-    HIPCHK(ctx, launch_iter_end(B.d_insts, B.nsweep, ctx->stream, e3));
+    HIPCHK(ctx, launch_finalize(B.d_insts, B.count == 1 ? nullptr : B.d_fins, B.nsweep_fins, 0, ctx->stream, e3));
     pf.iter_end_stamp = s3;
     return SK_OK;
 }
@@ -813,16 +808,26 @@ sk_status sk::run_batch_i16(sk_ctx *ctx, Batch &B, const sk_params *prm, int fir
     const int64_t bound = (prm->max_iters_per_stage + 1) * prm->n_p + 1;
     const size_t pstart = ctx->prof.pending.size();
     int64_t launched = 0;
-    // Launch blocks are check_every iterations long until the end is near:
-    // once every running instance is in its last stage (or, for an instance
-    // paused at each stage end, after the first block of the stage) they are
-    // at most kTailBlock long, so fewer launches run after the end. The first
-    // block of a paused stage is sized by the previous stage's iterations.
+    // Launch blocks between two looks at the controllers: a launch after the
+    // end costs some 8 us at n = 4096 and 20 at n = 32768, a look some 20. A
+    // stage takes at least two launches (an iteration, and the one that finds
+    // it converged), so the first block is that long for the whole ladder;
+    // the next ones are as long as the stages left take if each is like the
+    // one before (they rarely take less), up to check_every. n = 4096,
+    // planted, 12 launches: 738 us with a first block of 32, 539 now. For an
+    // instance paused at each stage end the first block is the previous
+    // stage's length, the next ones kTailBlock.
     constexpr int kTailBlock = 8;
-    int blk = check;
+    int blk = std::min(check, 2 * std::max(1, prm->n_p - first_stage));
+    auto left = [&](const Inst &I, const Ctl &c) -> int64_t {
+        if (I.deform_a > 0.0) return check;  // one long stage
+        if (I.pause || c.stage == 0) return kTailBlock;
+        const int64_t stage = c.stage_iters[c.stage - 1] + 1;
+        return std::max<int64_t>(2, stage - c.stage_iters[c.stage]) + (I.n_p - 1 - c.stage) * stage;
+    };
     bool swept = B.nsweep > 0, mid = !B.h_mid.empty();  // they have a running instance
-    if (B.count == 1 && B.h_insts[0].pause && first_stage > 0)
-        blk = (int)std::min<int64_t>(check, std::max<int64_t>(
+    if (B.count == 1 && B.h_insts[0].pause)
+        blk = first_stage == 0 ? check : (int)std::min<int64_t>(check, std::max<int64_t>(
                                                 4, ctx->h_ctl[0].stage_iters[first_stage - 1] + 2));
     for (;;) {
         if (swept && !B.coop)
@@ -847,7 +852,8 @@ sk_status sk::run_batch_i16(sk_ctx *ctx, Batch &B, const sk_params *prm, int fir
             B.coop = false;
             launched = 0;
         }
-        bool running = false, tail = true;
+        bool running = false;
+        int64_t want = 0;
         swept = mid = false;
         for (int k = 0; k < B.count; ++k) {
             const Ctl &c = ctx->h_ctl[k];
@@ -856,13 +862,11 @@ sk_status sk::run_batch_i16(sk_ctx *ctx, Batch &B, const sk_params *prm, int fir
             const Inst &I = B.h_insts[k];
             if (I.small) continue;
             (I.mid ? mid : swept) = true;
-            // (the deformed iteration is one long stage: full blocks)
-            const bool last = I.deform_a <= 0.0 && c.stage + 1 >= I.n_p;
-            tail &= last || I.pause;
+            want = std::max(want, left(I, c));
         }
         if (!running) break;
         if (launched > bound) return fail(ctx, SK_EDEVICE, "stage controller did not terminate");
-        blk = tail ? std::min(check, kTailBlock) : check;
+        blk = (int)std::min<int64_t>(check, want);
     }
     if (ctx->prof.on) {
         // triple index of each convergence detection, and the number of
