@@ -20,8 +20,7 @@ namespace {
 __device__ __forceinline__ float pow2_frac(double e2) {
     const double m = rint(e2);
     const float x = (float)((e2 - m) * kLn2D);
-    // |m| > 400 is far outside the FP32 range either way (0 or +inf)
-    return ldexpf(exp_frac(x), (int)fmin(fmax(m, -400.0), 400.0));
+    return ldexpf(exp_frac(x), sat_i32(m));
 }
 
 template <int CH>

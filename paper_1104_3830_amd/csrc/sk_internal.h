@@ -357,8 +357,7 @@ hipError_t launch_fused(const Inst *d_insts, int inst, int n, int grid, int stor
                         hipStream_t st);
 hipError_t launch_gather_ctl(const Inst *d_insts, int count, Ctl *out, hipStream_t st);
 // real-valued log-weights (sk_real.hip)
-hipError_t launch_real_minmax(const float *W, int n, int64_t pitch, int grid, float *part,
-                              hipStream_t st);
+hipError_t launch_real_minmax(const float *W, int64_t count, int grid, float *part, hipStream_t st);
 hipError_t launch_init_real(const Inst *d_insts, const RowUnit *d_units, int nunits, int grid, int cold,
                             hipStream_t st);
 hipError_t launch_row_sweep_real(const Inst *d_insts, const RowUnit *d_units, int nunits, int grid,

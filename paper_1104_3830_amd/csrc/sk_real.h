@@ -18,12 +18,20 @@ namespace sk {
 constexpr double kLog2eD = 1.4426950408889634;
 constexpr double kLn2D = 0.6931471805599453;
 
+// An integral double as an int32, saturated: what the instruction does, and a
+// C++ conversion leaves undefined. Clamping in FP64 first took two of a
+// term's nine FP64 instructions (n = 8192: row sweep 51.0 -> 48.9 us, column
+// sweep 61.9 -> 60.7).
+__device__ __forceinline__ int sat_i32(double m) {
+    int r;
+    asm("v_cvt_i32_f64 %0, %1" : "=v"(r) : "v"(m));
+    return r;
+}
+
 __device__ __forceinline__ float pow2_split(double e2) {
     const double m = rint(e2);
     const float f = (float)(e2 - m);
-    // |m| > 400 is far outside the FP32 range either way (0 or +inf)
-    const int mi = (int)fmin(fmax(m, -400.0), 400.0);
-    return ldexpf(ex2(f), mi);
+    return ldexpf(ex2(f), sat_i32(m));
 }
 
 // p of the current stage (of the current iteration, deformed) of a

@@ -37,7 +37,7 @@ sk_status plan_real(sk_ctx *ctx, Bump &bump, const float *W, int32_t n, const sk
     float *d_part = tmp.take<float>(3 * (size_t)kMinmaxGrid);
     if (!d_part) return fail(ctx, SK_ENOMEM, "arena too small for the range scan");
     const int grid = std::min(kMinmaxGrid, n);
-    HIPCHK(ctx, launch_real_minmax(W, n, n, grid, d_part, ctx->stream));
+    HIPCHK(ctx, launch_real_minmax(W, (int64_t)n * n, grid, d_part, ctx->stream));
     float *h = reinterpret_cast<float *>(ctx->h_checkout);  // pinned, >= 3 * kMinmaxGrid floats
     HIPCHK(ctx, hipMemcpyAsync(h, d_part, sizeof(float) * 3 * (size_t)grid, hipMemcpyDeviceToHost,
                                ctx->stream));
