@@ -22,7 +22,6 @@
 namespace sk {
 
 constexpr int kFT = 1024;    // threads per workgroup
-constexpr int kFR = 2;       // rows per group
 // rows per workgroup at most: ceil(n / grid) with n <= kLdsMaxN (the single
 // pass takes no larger instance) and a grid of
 // min(kFusedSlots, max(1, n / 2)) workgroups (64 at n = 16384, at most 3 for
@@ -85,9 +84,9 @@ __device__ __forceinline__ float sum_partials(float x) {
 // lane forms S_i from the NW partials. The scalar work of row i (its new
 // potentials and residual) is done by lane 0 of wave (i - r0) mod NW, so no
 // single wave falls behind at every barrier.
-template <int FT, int CPT, int FR, int NB, bool SENT, bool NT>
+template <int FT, int CPT, int FR, int NB, bool REG, bool SENT, bool NT>
 __device__ __forceinline__ void fused_i16_body(const Inst &I, Ctl *ctl, const float *tab,
-                                               float (*red)[FT / kWave][kFR], int *redm,
+                                               float (*red)[FT / kWave][FR], int *redm,
                                                float *reds, float *wres, int2 *gc, int *sF,
                                                float *sphi) {
     constexpr int NW = FT / kWave;
@@ -105,19 +104,23 @@ __device__ __forceinline__ void fused_i16_body(const Inst &I, Ctl *ctl, const fl
     float *phin_p = I.phi[par ^ 1];
     int c0[CPT];
     bool own[CPT];
-    // per owned column (4 G_j, exp(gam_j)) in one 8-byte LDS word at
-    // gc[(k * 8 + c) * FT + t] (the lanes of a wave read consecutive words),
-    // which leaves the registers to the terms of FR rows
+    // per owned column (4 G_j, exp(gam_j)): in registers, or in one 8-byte LDS
+    // word at gc[(k * 8 + c) * FT + t] (the lanes of a wave read consecutive
+    // words), which leaves the registers to the terms of FR rows
     float acc[CPT][8];
+    int2 gr[REG ? CPT : 1][8];
+    auto col = [&](int k, int c) { return REG ? gr[k][c] : gc[(k * 8 + c) * FT + t]; };
 #pragma unroll
     for (int k = 0; k < CPT; ++k) {
         c0[k] = (t + k * FT) * 8;
         own[k] = c0[k] < n;
 #pragma unroll
         for (int c = 0; c < 8; ++c) {
-            gc[(k * 8 + c) * FT + t] =
+            const int2 ag =
                 own[k] ? make_int2(4 * gld(I.G + c0[k] + c), __float_as_int(fex2(gld(I.gam + c0[k] + c) * kL2e)))
                        : make_int2(0, 0);
+            if (REG) gr[k][c] = ag;
+            else gc[(k * 8 + c) * FT + t] = ag;
             acc[k][c] = 0.f;
         }
     }
@@ -160,7 +163,7 @@ __device__ __forceinline__ void fused_i16_body(const Inst &I, Ctl *ctl, const fl
                     unpack8i(cur[rr][k], w);
 #pragma unroll
                     for (int c = 0; c < 8; ++c) {
-                        const int2 ag = gc[(k * 8 + c) * FT + t];
+                        const int2 ag = col(k, c);
                         float e = tab_at(tab, tab_off(p4, w[c], ag.x, B));
                         if (SENT) e = (w[c] == SK_SENTINEL) ? 0.f : e;
                         T[rr][k][c] = e;
@@ -208,7 +211,7 @@ __device__ __forceinline__ void fused_i16_body(const Inst &I, Ctl *ctl, const fl
 #pragma unroll
                 for (int c = 0; c < 8; ++c)
                     if (!SENT || w[c] != SK_SENTINEL)
-                        m4 = max(m4, __mul24(p4, w[c]) + gc[(k * 8 + c) * FT + t].x + 4 * Fi[rr]);
+                        m4 = max(m4, __mul24(p4, w[c]) + col(k, c).x + 4 * Fi[rr]);
             }
             m4 = wave_max_i(m4);
             if (lane == 0) redm[wave] = m4;
@@ -224,7 +227,7 @@ __device__ __forceinline__ void fused_i16_body(const Inst &I, Ctl *ctl, const fl
                 unpack8i(cur[rr][k], w);
 #pragma unroll
                 for (int c = 0; c < 8; ++c) {
-                    const int2 ag = gc[(k * 8 + c) * FT + t];
+                    const int2 ag = col(k, c);
                     float e = mm == INT_MIN ? 0.f
                                             : tab_at(tab, tab_off(p4, w[c], ag.x, 4 * (Fi[rr] - M - kTabLo)));
                     if (SENT) e = (w[c] == SK_SENTINEL) ? 0.f : e;
@@ -287,7 +290,7 @@ __device__ __forceinline__ void fused_i16_body(const Inst &I, Ctl *ctl, const fl
         if (own[k]) {
 #pragma unroll
             for (int c = 0; c < 8; ++c)
-                if (c0[k] + c < n) gst(dst + c0[k] + c, acc[k][c] * __int_as_float(gc[(k * 8 + c) * FT + t].y));
+                if (c0[k] + c < n) gst(dst + c0[k] + c, acc[k][c] * __int_as_float(col(k, c).y));
         }
     // residual slot of this workgroup: lane 0 of every wave formed the
     // residuals of its rows
@@ -301,7 +304,9 @@ __device__ __forceinline__ void fused_i16_body(const Inst &I, Ctl *ctl, const fl
 }
 
 // Two shapes, both 1024 threads (four waves per SIMD, 128 VGPRs): n <= 8192
-// takes one chunk per thread and two rows per group, one group ahead; larger
+// takes one chunk per thread and two rows per group, one group ahead, the
+// column data in registers (122 VGPRs; 41.4 us at n = 8192, from LDS 43.9;
+// three rows per group 42.3, two groups ahead from LDS 45.4); larger
 // n two chunks per thread and one row per group, two rows ahead (12 bytes
 // of spill). Measured at n = 16384: with the row potentials read from global
 // memory per row instead of LDS, 150.5 us; one row ahead 143.0 us, two rows
@@ -309,23 +314,23 @@ __device__ __forceinline__ void fused_i16_body(const Inst &I, Ctl *ctl, const fl
 // 512 threads with four chunks each (two waves per SIMD, 238 VGPRs, up to
 // three rows ahead) 160-163 us at every depth.
 constexpr int kFusedAhead = 2;
-template <int FT, int CPT, int FR, int NB, bool NT>
+template <int FT, int CPT, int FR, int NB, bool REG, bool NT>
 __global__ __launch_bounds__(FT) void k_fused_i16(const Inst *__restrict__ insts, int inst) {
     __shared__ int sF[kFusedRows];
     __shared__ float sphi[kFusedRows];
     __shared__ float tab[kTabN];
-    __shared__ float red[2][FT / kWave][kFR];
+    __shared__ float red[2][FT / kWave][FR];
     __shared__ int redm[FT / kWave];
     __shared__ float reds[FT / kWave];
     __shared__ float wres[FT / kWave];
-    __shared__ int2 gc[CPT * 8 * FT];
+    __shared__ int2 gc[REG ? 1 : CPT * 8 * FT];
     const Inst &I = insts[inst];
     Ctl *ctl = I.ctl;
     if (ctl->state != ST_RUNNING) return;
     fill_exp_table(tab);
     __syncthreads();
-    if (ctl->sent != 0u) fused_i16_body<FT, CPT, FR, NB, true, NT>(I, ctl, tab, red, redm, reds, wres, gc, sF, sphi);
-    else fused_i16_body<FT, CPT, FR, NB, false, NT>(I, ctl, tab, red, redm, reds, wres, gc, sF, sphi);
+    if (ctl->sent != 0u) fused_i16_body<FT, CPT, FR, NB, REG, true, NT>(I, ctl, tab, red, redm, reds, wres, gc, sF, sphi);
+    else fused_i16_body<FT, CPT, FR, NB, REG, false, NT>(I, ctl, tab, red, redm, reds, wres, gc, sF, sphi);
 }
 
 // ---------------------------------------------------------------- stored K
@@ -514,9 +519,9 @@ static hipError_t launch_fused_nt(const Inst *d_insts, int inst, int n, int grid
                                   hipStream_t st) {
     if (storage == SK_W_I16) {
         if ((n / 8 + kFT - 1) / kFT <= 1)
-            hipLaunchKernelGGL((k_fused_i16<kFT, 1, 2, 2, NT>), dim3(grid), dim3(kFT), 0, st, d_insts, inst);
+            hipLaunchKernelGGL((k_fused_i16<kFT, 1, 2, 2, true, NT>), dim3(grid), dim3(kFT), 0, st, d_insts, inst);
         else
-            hipLaunchKernelGGL((k_fused_i16<kFT, 2, 1, kFusedAhead + 1, NT>), dim3(grid), dim3(kFT), 0, st,
+            hipLaunchKernelGGL((k_fused_i16<kFT, 2, 1, kFusedAhead + 1, false, NT>), dim3(grid), dim3(kFT), 0, st,
                                d_insts, inst);
         return hipGetLastError();
     }
