@@ -373,26 +373,38 @@ constexpr int kFinThreads = kFinWaves * kWave;
 static_assert(kMaxN / kFinCols < 0x10000 && kRowResSlots <= kFinThreads, "");
 static_assert(kFinCols == kWave, "a wave of the finalise owns a slot's columns");
 
-__device__ void stage_advance(const Inst &I, Ctl *ctl, int par) {
+// Row and column potential i of instance I, from buffer par, times ratio.
+__device__ __forceinline__ void rescale_potential(const Inst &I, int par, double ratio, int i) {
+    const double f = ((double)I.F[par][i] + (double)I.phi[par][i]) * ratio;
+    const double g = ((double)I.G[i] + (double)I.gam[i]) * ratio;
+    const double k = rint(f);
+    I.F[0][i] = (int32_t)k;
+    I.phi[0][i] = (float)(f - k);
+    const double kg = rint(g);
+    I.G[i] = (int32_t)kg;
+    I.gam[i] = (float)(g - kg);
+}
+__device__ __forceinline__ double stage_ratio(const Inst &I, int s) {
+    return (double)I.ladder[s + 1] / (double)I.ladder[s];
+}
+// Whether the end of stage s moves on to the next p on the device.
+__device__ __forceinline__ bool stage_moves_on(const Inst &I, int s) {
+    return I.deform_a <= 0.0 && I.storage == SK_W_I16 && !I.pause && s + 1 < I.n_p;
+}
+
+// moved: the potentials have been rescaled.
+__device__ void stage_advance(const Inst &I, Ctl *ctl, int par, bool moved) {
     const int n = I.n;
     const int s = ctl->stage;
     if (s + 1 < I.n_p) {
-        const int p0 = I.ladder[s], p1 = I.ladder[s + 1];
-        const double ratio = (double)p1 / (double)p0;
-        for (int i = threadIdx.x; i < n; i += blockDim.x) {
-            const double f = ((double)I.F[par][i] + (double)I.phi[par][i]) * ratio;
-            const double k = rint(f);
-            I.F[0][i] = (int32_t)k;
-            I.phi[0][i] = (float)(f - k);
-            const double g = ((double)I.G[i] + (double)I.gam[i]) * ratio;
-            const double kg = rint(g);
-            I.G[i] = (int32_t)kg;
-            I.gam[i] = (float)(g - kg);
+        if (!moved) {
+            const double ratio = stage_ratio(I, s);
+            for (int i = threadIdx.x; i < n; i += blockDim.x) rescale_potential(I, par, ratio, i);
+            __syncthreads();
         }
-        __syncthreads();
         if (threadIdx.x == 0) {
             ctl->stage = s + 1;
-            ctl->p = p1;
+            ctl->p = I.ladder[s + 1];
             ctl->iter = 0;
         }
     } else {
@@ -405,7 +417,7 @@ __device__ void stage_advance(const Inst &I, Ctl *ctl, int par) {
 // path pauses (ST_STAGE_END) so the host can fold the scalings, move to the
 // next p and recompute K; so does an instance whose host evaluates every
 // stage (certificate, reduced matrix, ratio) before raising p.
-__device__ void end_stage(const Inst &I, Ctl *ctl, int par) {
+__device__ void end_stage(const Inst &I, Ctl *ctl, int par, bool moved) {
     if (I.deform_a > 0.0) {
         // the deformed iteration is a single stage
         __syncthreads();
@@ -413,7 +425,7 @@ __device__ void end_stage(const Inst &I, Ctl *ctl, int par) {
         return;
     }
     if (I.storage == SK_W_I16 && !I.pause) {
-        stage_advance(I, ctl, par);
+        stage_advance(I, ctl, par, moved);
     } else {
         __syncthreads();
         if (threadIdx.x == 0) ctl->state = ST_STAGE_END;
@@ -507,7 +519,7 @@ __device__ void iteration_end(const Inst &I, Ctl *ctl, float res, bool conv, Ite
     if (ctl->state != ST_RUNNING) return;
     if (conv) {
         if (threadIdx.x == 0) ctl->last_res = res;
-        end_stage(I, ctl, iter & 1);
+        end_stage(I, ctl, iter & 1, stage_moves_on(I, ctl->stage));
         return;
     }
     // commit: the new row potentials are in buffer npar, i.e. (iter+1) & 1
@@ -520,7 +532,7 @@ __device__ void iteration_end(const Inst &I, Ctl *ctl, float res, bool conv, Ite
     __syncthreads();
     if ((int64_t)(iter + 1) >= I.max_iters) {
         if (threadIdx.x == 0) ctl->capped += 1;
-        end_stage(I, ctl, npar);
+        end_stage(I, ctl, npar, false);
     } else if (I.deform_a > 0.0 && threadIdx.x == 0) {
         // deformed iteration: the next iteration's p, potentials unscaled
         ctl->p = deform_p(I, iter + 2);
@@ -639,6 +651,11 @@ __global__ __launch_bounds__(kFinThreads) void k_col_finalize(const Inst *__rest
             if (lane == 0 && drift > 0.f) atomicMax(&ctl->drift_bits, __float_as_uint(drift));
         }
     }
+    // a converged stage: each workgroup moves its rows and columns to the next
+    // p (nothing else of this launch reads them); the last one, alone, took 4
+    // us more at n = 4096 (a planted solve, 6 stages: 535 -> 518 us)
+    if (wave == 0 && conv && !err && j < n && stage_moves_on(I, stage))
+        rescale_potential(I, iter & 1, stage_ratio(I, stage), j);
     // The last workgroup reads what others wrote in this launch in two cases
     // only: a list of flagged columns, and potentials that move to the next p
     // because the stage is capped. Wave 0 alone wrote, so its own fence before

@@ -1,5 +1,5 @@
 // Device helpers of the real-valued log-weight path (W = log A as float32,
-// -inf for a zero entry), shared by its kernels and the end-of-iteration
+// -inf for a zero entry), shared by its kernels and the finalise
 // kernel.
 //
 // A term exp(E), E = p (w_ij - wref) + log u_i + log v_j, is formed from the

@@ -2,7 +2,7 @@
 // recheck and reduced matrix for W = log A given as float32 (-inf for a zero
 // entry). The terms are formed as described in sk_real.h; everything else
 // (potentials layout, fixed-slot column partials, the finalise kernel's
-// column step, residual slots, the end-of-iteration controller) is shared
+// column step, residual slots, the controller) is shared
 // with the int16 path.
 //
 // Layout: W row-major with pitch I.pitch floats. With n % 4 == 0, a pitch
