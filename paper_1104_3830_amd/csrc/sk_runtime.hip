@@ -79,6 +79,10 @@ static int check_segs(int32_t n, const TilePlan &t) {
     const int seg = check_seg_rows(n, t);
     return (n + seg - 1) / seg;
 }
+// Segments whose column partials an instance's check scratch holds: the check
+// of a stored K sums the column sweep's segments, which a tuned table makes
+// shorter than the int16 check's.
+static int check_slots(int32_t n, const TilePlan &t) { return std::max(check_segs(n, t), t.nseg); }
 // Doubles of check scratch for a batch: all instances at once up to 32 MiB
 // (more go in groups), at least the largest instance's.
 static size_t check_scratch(size_t largest, size_t sum) {
@@ -97,7 +101,7 @@ size_t shared_bytes(int32_t count, const int32_t *n) {
         // an instance takes the 8-wide plan unless its W is misaligned
         // (then the 1-wide plan: no more slots, more column units)
         TilePlan t = plan_tiles(n[k], 1), t1 = plan_tiles(n[k], 0);
-        const size_t chk = check_doubles(n[k], check_segs(n[k], t));
+        const size_t chk = check_doubles(n[k], check_slots(n[k], t));
         chk_max = std::max(chk_max, chk);
         chk_sum += chk;
         ccols += (int64_t)((n[k] + kColTile8 - 1) / kColTile8) * check_segs(n[k], t);
@@ -524,7 +528,7 @@ sk_status sk::finish_tables(sk_ctx *ctx, Bump &bump, Batch &B) {
         if (B.count > 1)
             for (int s = 0; s < I.chk_nseg; ++s)
                 for (int tt = 0; tt * kColTile8 < I.n; ++tt) B.h_ccols.push_back(ColUnit{k, tt, s, 0});
-        const size_t chk = check_doubles(I.n, I.chk_nseg);
+        const size_t chk = check_doubles(I.n, std::max(I.chk_nseg, I.nseg));
         chk_max = std::max(chk_max, chk);
         chk_sum += chk;
     }
@@ -590,7 +594,7 @@ sk_status sk::finish_tables(sk_ctx *ctx, Bump &bump, Batch &B) {
     size_t chk_used = 0;
     for (int q = 0; q < B.count; ++q) {
         Inst &I = B.h_insts[B.order[q]];
-        const size_t chk = check_doubles(I.n, I.chk_nseg);
+        const size_t chk = check_doubles(I.n, std::max(I.chk_nseg, I.nseg));
         if (chk_used + chk > chk_cap) {
             B.chk_end.push_back(q);
             chk_used = 0;
