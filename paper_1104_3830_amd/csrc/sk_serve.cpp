@@ -440,7 +440,9 @@ static void serve_loop(Server *S) {
         }
         for (int it = 0; it < S->iters_per_tick && st == SK_OK && e == hipSuccess; ++it)
             if (S->B.nsweep > 0) st = iterate_i16(ctx, S->B);
-        if (st == SK_OK && e == hipSuccess) st = iterate_mid(ctx, S->B, S->iters_per_tick / 2);
+        // half as many of the middle instances' (an iteration of theirs is one
+        // launch), and at least a pair of launches
+        if (st == SK_OK && e == hipSuccess) st = iterate_mid(ctx, S->B, std::max(1, S->iters_per_tick / 2));
         if (st == SK_OK && e == hipSuccess) st = iterate_small(ctx, S->B, kServeSmallIters);
         if (st == SK_OK && e == hipSuccess) st = read_ctl(ctx, S->B);
         if (st != SK_OK || e != hipSuccess) {
