@@ -349,9 +349,6 @@ __device__ __forceinline__ void coop_run(const Inst &I, CoopLds<CH> &L, typename
             gamn = neg_log_split(T, k);
             Gn = G + k;
         }
-        // a fraction that rounding took past 1/2, as the launched iteration
-        // finds it when it reads the potentials
-        if constexpr (!Pol::kKeep) unit_frac(Gn, gamn);
         if (next) {
             // the next p, with p^-1 log v held (FP64)
             const double x = ((double)Gn + (double)gamn) * ratio, k = rint(x);
@@ -393,10 +390,6 @@ __device__ __forceinline__ void coop_run(const Inst &I, CoopLds<CH> &L, typename
             F = Fn;
             phi = phin;
             rc = rn;
-            if constexpr (!Pol::kKeep) {
-                unit_frac(F, phi);
-                if (__ballot(F != Fn) != 0ull) rc = exp_frac(phi);
-            }
             if (iter >= 1) last_res = rmax;
             ++iter;
             ++done;

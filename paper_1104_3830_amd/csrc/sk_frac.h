@@ -5,7 +5,7 @@
 // over its hundreds of iterations.
 #pragma once
 
-#include "sk_internal.h"
+#include <hip/hip_runtime.h>
 
 namespace sk {
 
@@ -45,11 +45,12 @@ __device__ __forceinline__ void unit_frac(int &k, float &f) {
     f -= r;
 }
 
-// -log(S) = k + f with k an integer and |f| <= 1/2, for S in [2^-64, 2^64].
+// -log(S) = k + f with k an integer, for S in [2^-64, 2^64]; |f| is at most 1/2
+// and what the choice of k leaves out (64 kLo and a rounding, under 1e-4).
 // S = 2^e m, m in [1/sqrt 2, sqrt 2); with y = m - 1 (exact) and
 // s = y / (2 + y), log m = 2 atanh(s) = y - s y + s^3 (2/3 + 2/5 s^2 + ...).
 // e log 2 is split so that its leading part and k cancel exactly.
-__device__ __forceinline__ float neg_log_split(float S, int &k) {
+__device__ __forceinline__ float neg_log_parts(float S, int &k) {
     float m = __builtin_amdgcn_frexp_mantf(S);  // [1/2, 1)
     int e = __builtin_amdgcn_frexp_expf(S);
     const bool low = m < 0.70710678f;
@@ -72,11 +73,17 @@ __device__ __forceinline__ float neg_log_split(float S, int &k) {
     return (fmaf(-ef, kHi, -kf) - y) - fmaf(ef, kLo, corr);
 }
 
-// S in float64: S = T + d with T its float32 rounding, log S = log T + d / T.
+// -log(S) = k + f with |f| <= 1/2, exactly the k and f that unit_frac leaves as
+// they are: a potential has one form, whether it is kept on chip from one
+// iteration to the next, read back by the next launch, or by a caller who
+// resumes from it. S in float64: S = T + d with T its float32 rounding,
+// log S = log T + d / T.
 __device__ __forceinline__ float neg_log_split(double S, int &k) {
     const float T = (float)S;
     const float d = (float)(S - (double)T);
-    return neg_log_split(T, k) - d * __builtin_amdgcn_rcpf(T);
+    float f = neg_log_parts(T, k) - d * __builtin_amdgcn_rcpf(T);
+    unit_frac(k, f);
+    return f;
 }
 
 }  // namespace sk
