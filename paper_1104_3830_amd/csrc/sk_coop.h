@@ -24,8 +24,11 @@
 //
 // Every wait is bounded: a workgroup that runs out of polls (the others could
 // not become resident) leaves without its share of the result, and the commit
-// kernel then drops the whole launch, which has written nothing but staging
-// copies. The caller goes on with the launch-per-iteration kernel.
+// kernel then drops the whole launch. Shares go to the second copies of the
+// potentials; the first row copy always holds the state a launch starts from,
+// and the commit of a dropped launch writes it over what others may have left
+// in the second (which the sweeps read at an odd iteration). The caller goes
+// on with the launch-per-iteration kernel, or the sweeps.
 #pragma once
 
 #include <climits>
@@ -77,8 +80,8 @@ struct CoopSeq4 {
 // Polls the K words p(0) .. p(K - 1), all in flight together, until each has
 // sequence number s. False when the spins ran out.
 template <int K, class Seq, class P>
-__device__ __forceinline__ bool coop_poll(P p, uint32_t s, CoopWord (&x)[K]) {
-    for (int spin = 0; spin < kCoopSpins; ++spin) {
+__device__ __forceinline__ bool coop_poll(P p, uint32_t s, int spins, CoopWord (&x)[K]) {
+    for (int spin = 0; spin < spins; ++spin) {
         bool all = true;
 #pragma unroll
         for (int k = 0; k < K; ++k) x[k] = coop_get(p(k));
@@ -108,12 +111,15 @@ constexpr int kCoopBail = -(1 << 27);              // G of a column whose sum le
 // next, and only those of rows and columns whose integer parts moved are
 // formed again (terms that cost more than their table read).
 template <class Pol, int CH>
-__device__ __forceinline__ void coop_run(const Inst &I, CoopLds<CH> &L, typename Pol::Lds &LP, int budget) {
+__device__ __forceinline__ void coop_run(const Inst &I, CoopLds<CH> &L, typename Pol::Lds &LP, int budget,
+                                         CoopGiveUp give_up) {
     constexpr int C = 8 * CH, R = kCoopR, RL = kCoopRL;
     const int t = (int)threadIdx.x, lane0 = t % kWave;
     const int wave = __builtin_amdgcn_readfirstlane(t / kWave);
     const int n = I.n, n8 = pad8(n) >> 3, nblk = (int)gridDim.x, blk = (int)blockIdx.x;
     const float tol = I.tol;
+    const int spins = give_up.polls > 0 ? give_up.polls : kCoopSpins;
+    if (give_up.polls > 0 && blk == give_up.workgroup) return;
     Ctl *ctl = I.ctl;
     CoopHdr *hdr = reinterpret_cast<CoopHdr *>(I.coop);
     CoopWord *base = reinterpret_cast<CoopWord *>(I.coop) + sizeof(CoopHdr) / 8;
@@ -308,14 +314,14 @@ __device__ __forceinline__ void coop_run(const Inst &I, CoopLds<CH> &L, typename
             CoopWord x[kMidMaxBlocks * kMidRows / kCoopThreads];
             constexpr int K = kMidMaxBlocks * kMidRows / kCoopThreads, Q = kCoopThreads / kMidRows;
             good &= coop_poll<K, CoopSeq32>(
-                [&](int k) { return src + (int64_t)min(t / kMidRows + Q * k, nblk - 1) * slot; }, seq, x);
+                [&](int k) { return src + (int64_t)min(t / kMidRows + Q * k, nblk - 1) * slot; }, seq, spins, x);
 #pragma unroll
             for (int k = 0; k < K; ++k) L.slot[t / kMidRows + Q * k][t % kMidRows] = __uint_as_float((uint32_t)x[k]);
         }
         if (wave == kCoopWaves - 1) {
             CoopWord x[1];
             good &= coop_poll<1, CoopSeq32>(
-                [&](int) { return wresid + buf * kMidMaxBlocks + min(lane, nblk - 1); }, seq, x);
+                [&](int) { return wresid + buf * kMidMaxBlocks + min(lane, nblk - 1); }, seq, spins, x);
             const uint32_t b = (uint32_t)x[0];
             const float m = wave_max_v(b == kCoopErr ? 0.f : __uint_as_float(b));
             if (b == kCoopErr) L.err = ERR_EMPTY_ROW;
@@ -367,7 +373,7 @@ __device__ __forceinline__ void coop_run(const Inst &I, CoopLds<CH> &L, typename
         {
             CoopWord x[kCoopCT];
             good = kCoopCT * t >= n || coop_poll<kCoopCT, CoopSeq4>(
-                [&](int k) { return wcol + buf * slot + min(kCoopCT * t + k, n - 1); }, seq, x);
+                [&](int k) { return wcol + buf * slot + min(kCoopCT * t + k, n - 1); }, seq, spins, x);
             if (!good) L.fail = 1u;
 #pragma unroll
             for (int q = 0; q < kCoopCT; ++q) {
@@ -414,6 +420,7 @@ __device__ __forceinline__ void coop_run(const Inst &I, CoopLds<CH> &L, typename
             iter = 0;
         }
     }
+    if (blk == give_up.workgroup) return;
     // ---- this workgroup's share, into the second copies (k_coop_commit)
     if (row_on && lane0 % RL == 0) {
         I.F[1][r] = F;

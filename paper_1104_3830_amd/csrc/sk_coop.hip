@@ -92,24 +92,27 @@ struct CoopInt {
 };
 
 template <int CH, bool SENT>
-__device__ __forceinline__ void coop_int(const Inst &I, int budget, CoopLds<CH> &L, typename CoopInt<CH, SENT>::Lds &LP) {
-    coop_run<CoopInt<CH, SENT>, CH>(I, L, LP, budget);
+__device__ __forceinline__ void coop_int(const Inst &I, int budget, CoopGiveUp give_up, CoopLds<CH> &L,
+                                         typename CoopInt<CH, SENT>::Lds &LP) {
+    coop_run<CoopInt<CH, SENT>, CH>(I, L, LP, budget, give_up);
 }
 
 template <int CH>
-__global__ __launch_bounds__(kCoopThreads, 1) void k_coop(const Inst *__restrict__ insts, int budget) {
+__global__ __launch_bounds__(kCoopThreads, 1) void k_coop(const Inst *__restrict__ insts, int budget,
+                                                          CoopGiveUp give_up) {
     __shared__ CoopLds<CH> L;
     // (one layout whether W holds absent entries or not)
     __shared__ typename CoopInt<CH, false>::Lds LP;
     const Inst &I = insts[0];
     if (__builtin_amdgcn_readfirstlane(I.ctl->state) != ST_RUNNING) return;
     if (__builtin_amdgcn_readfirstlane(I.ctl->sent) != 0u)
-        coop_int<CH, true>(I, budget, L, reinterpret_cast<typename CoopInt<CH, true>::Lds &>(LP));
+        coop_int<CH, true>(I, budget, give_up, L, reinterpret_cast<typename CoopInt<CH, true>::Lds &>(LP));
     else
-        coop_int<CH, false>(I, budget, L, LP);
+        coop_int<CH, false>(I, budget, give_up, L, LP);
 }
 
-// Takes the launch's result over if every workgroup left its share.
+// Takes the launch's result over if every workgroup left its share; otherwise
+// the second copy of the row potentials gets the start's state back.
 __global__ __launch_bounds__(256) void k_coop_commit(const Inst *__restrict__ insts, int nblk) {
     const Inst &I = insts[0];
     const int n = I.n, i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -120,6 +123,9 @@ __global__ __launch_bounds__(256) void k_coop_commit(const Inst *__restrict__ in
         I.phi[0][i] = I.phi[1][i];
         I.G[i] = I.G2[i];
         I.gam[i] = I.gam2[i];
+    } else if (i < n && I.ctl->state == ST_RUNNING) {
+        I.F[1][i] = I.F[0][i];
+        I.phi[1][i] = I.phi[0][i];
     }
     if (blockIdx.x > 0 || threadIdx.x >= kWave) return;
     Ctl *c = I.ctl;
@@ -165,15 +171,15 @@ hipError_t launch_coop_clear(const Inst *d_insts, int n, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t launch_coop(const Inst *d_insts, int n, int real, int budget, hipStream_t st) {
+hipError_t launch_coop(const Inst *d_insts, int n, int real, int budget, CoopGiveUp give_up, hipStream_t st) {
     const int nblk = (n + kMidRows - 1) / kMidRows;
     hipLaunchKernelGGL(k_coop_begin, dim3(1), dim3(1), 0, st, d_insts);
     if (real)
-        launch_coop_real(d_insts, n, nblk, budget, st);
+        launch_coop_real(d_insts, n, nblk, budget, give_up, st);
     else if (n <= 512)
-        hipLaunchKernelGGL(k_coop<1>, dim3(nblk), dim3(kCoopThreads), 0, st, d_insts, budget);
+        hipLaunchKernelGGL(k_coop<1>, dim3(nblk), dim3(kCoopThreads), 0, st, d_insts, budget, give_up);
     else
-        hipLaunchKernelGGL(k_coop<2>, dim3(nblk), dim3(kCoopThreads), 0, st, d_insts, budget);
+        hipLaunchKernelGGL(k_coop<2>, dim3(nblk), dim3(kCoopThreads), 0, st, d_insts, budget, give_up);
     hipLaunchKernelGGL(k_coop_commit, dim3((n + 255) / 256), dim3(256), 0, st, d_insts, nblk);
     return hipGetLastError();
 }

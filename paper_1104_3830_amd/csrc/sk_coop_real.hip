@@ -106,21 +106,22 @@ struct CoopReal {
 };
 
 template <int CH>
-__global__ __launch_bounds__(kCoopThreads, 1) void k_coop_real(const Inst *__restrict__ insts, int budget) {
+__global__ __launch_bounds__(kCoopThreads, 1) void k_coop_real(const Inst *__restrict__ insts, int budget,
+                                                               CoopGiveUp give_up) {
     __shared__ CoopLds<CH> L;
     __shared__ typename CoopReal<CH>::Lds LP;
     const Inst &I = insts[0];
     if (__builtin_amdgcn_readfirstlane(I.ctl->state) != ST_RUNNING) return;
-    coop_run<CoopReal<CH>, CH>(I, L, LP, budget);
+    coop_run<CoopReal<CH>, CH>(I, L, LP, budget, give_up);
 }
 
 }  // namespace
 
-void launch_coop_real(const Inst *d_insts, int n, int nblk, int budget, hipStream_t st) {
+void launch_coop_real(const Inst *d_insts, int n, int nblk, int budget, CoopGiveUp give_up, hipStream_t st) {
     if (n <= 512)
-        hipLaunchKernelGGL(k_coop_real<1>, dim3(nblk), dim3(kCoopThreads), 0, st, d_insts, budget);
+        hipLaunchKernelGGL(k_coop_real<1>, dim3(nblk), dim3(kCoopThreads), 0, st, d_insts, budget, give_up);
     else
-        hipLaunchKernelGGL(k_coop_real<2>, dim3(nblk), dim3(kCoopThreads), 0, st, d_insts, budget);
+        hipLaunchKernelGGL(k_coop_real<2>, dim3(nblk), dim3(kCoopThreads), 0, st, d_insts, budget, give_up);
 }
 
 }  // namespace sk

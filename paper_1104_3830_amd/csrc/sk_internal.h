@@ -317,9 +317,15 @@ hipError_t launch_finalize(const Inst *d_insts, const FinUnit *d_units, int nuni
 // area, cleared once per run, and up to `budget` iterations per launch.
 size_t coop_bytes(int n);
 hipError_t launch_coop_clear(const Inst *d_insts, int n, hipStream_t st);
-// real: real-valued log-weights (sk_coop_real.hip).
-hipError_t launch_coop(const Inst *d_insts, int n, int real, int budget, hipStream_t st);
-void launch_coop_real(const Inst *d_insts, int n, int nblk, int budget, hipStream_t st);
+// real: real-valued log-weights (sk_coop_real.hip). give_up: a test's, for a
+// launch that is to be dropped: the workgroup leaves without its share at the
+// launch's end, or at its start, the others then after that many polls of a
+// word (0: at the end).
+struct CoopGiveUp {
+    int workgroup = -1, polls = 0;
+};
+hipError_t launch_coop(const Inst *d_insts, int n, int real, int budget, CoopGiveUp give_up, hipStream_t st);
+void launch_coop_real(const Inst *d_insts, int n, int nblk, int budget, CoopGiveUp give_up, hipStream_t st);
 // The FP64 check. Tables of units, or for one instance (null) its index and
 // the number of its units; ended: only instances that are not running.
 hipError_t launch_check_rows(const Inst *d_insts, const RowUnit *d_units, int nunits, int grid, int ended,

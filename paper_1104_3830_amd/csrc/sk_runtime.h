@@ -158,6 +158,9 @@ struct sk_ctx {
     size_t h_csr_bytes = 0;
     sk::Batch scratch_batch;
     int absorbs = 0;
+    // resident launches until one that a test has given up (< 0: none)
+    int64_t give_up_launch = -1;
+    sk::CoopGiveUp give_up;
     double k_res_rows = 0, k_res_cols = 0;
     sk::Profiler prof;
     sk::Server *server = nullptr;

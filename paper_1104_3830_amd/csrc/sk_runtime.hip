@@ -223,6 +223,15 @@ sk_status sk_set_tile_table(const int32_t *n_max, const int32_t *seg_rows, int32
     return SK_OK;
 }
 
+// For tests alone, not part of the ABI: the context's resident launch number
+// `launch` from here is given up as CoopGiveUp says.
+extern "C" void sk_test_resident_give_up(sk_ctx *ctx, int launch, int workgroup, int polls) {
+    std::lock_guard<std::mutex> g(ctx->mu);
+    ctx->give_up_launch = launch;
+    ctx->give_up.workgroup = workgroup;
+    ctx->give_up.polls = polls;
+}
+
 sk_status sk_profile_enable(sk_ctx *ctx, int enable) {
     if (!ctx) return SK_EINVAL;
     std::lock_guard<std::mutex> g(ctx->mu);
@@ -842,6 +851,7 @@ sk_status sk::run_batch_i16(sk_ctx *ctx, Batch &B, const sk_params *prm, int fir
         sk_status s = SK_OK;
         if (B.coop)
             HIPCHK(ctx, PROF(ctx, KID_MID, launch_coop(B.d_insts, B.nmax, B.h_insts[0].Wr != nullptr, kSmallBudget,
+                                                       ctx->give_up_launch-- == 0 ? ctx->give_up : CoopGiveUp{},
                                                        ctx->stream)));
         else if (mid)
             s = iterate_mid(ctx, B, blk);
