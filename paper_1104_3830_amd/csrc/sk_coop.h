@@ -70,7 +70,11 @@ __device__ __forceinline__ CoopWord coop_get(const CoopWord *p) {
 }
 
 // Sequence number of a word: the upper half, or for column potentials the low
-// four bits of the half that holds G (|G| < 2^27).
+// four bits of the half that holds G. G has 28 bits there, fewer than the int32
+// it is kept in (a cold start reaches 0.7 of 2^27, and a caller's starting
+// potentials may split log u_i + log v_j anywhere): a column outside them
+// leaves the iteration to the launched kernels, as one whose sum left the safe
+// range does.
 struct CoopSeq32 {
     static __device__ __forceinline__ bool ok(CoopWord x, uint32_t s) { return (uint32_t)(x >> 32) == s; }
 };
@@ -104,7 +108,7 @@ struct CoopLds {
 };
 
 constexpr uint32_t kCoopErr = 0xffffffffu;         // residual word of a block with an empty row
-constexpr int kCoopBail = -(1 << 27);              // G of a column whose sum left the safe range
+constexpr int kCoopBail = -(1 << 27);              // G of a column that leaves the iteration to other kernels
 
 // Pol: the kind of weights. CH: chunks of 512 columns, 8 consecutive columns
 // of each per lane. Pol::kKeep: the terms are kept from one iteration to the
@@ -361,6 +365,7 @@ __device__ __forceinline__ void coop_run(const Inst &I, CoopLds<CH> &L, typename
             Gn = (int)k;
             gamn = (float)(x - k);
         }
+        flag |= own && (Gn <= kCoopBail || Gn >= -kCoopBail);
         if (error) {
             state = ST_ERROR;
             break;
