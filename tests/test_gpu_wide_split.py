@@ -30,6 +30,18 @@ def parts(pot, n):
     return raw[0].astype(np.int64), raw[1].view(np.float32), raw[2].astype(np.int64), raw[3].view(np.float32)
 
 
+@pytest.mark.parametrize("c", [3 << 26, 3 << 25, -(3 << 26), (1 << 27) - 1, 1 - (1 << 27)])
+@pytest.mark.parametrize("n", [64, 300, 1000])
+def test_int16_one_stage(ctx, n, c):
+    """Exponents are integer sums, in which c cancels: the same bits."""
+    W = torch.from_numpy(skgen.uniform_weights(n, 0, 40, seed=n)).cuda()
+    prm = sk.make_params([2], tol=0.0, max_iters=3, warm_start=True)
+    F0, p0, G0, g0 = parts(ctx.scale(W, prm, potentials=start(n, 0)).potentials, n)
+    F1, p1, G1, g1 = parts(ctx.scale(W, prm, potentials=start(n, c)).potentials, n)
+    assert np.array_equal(F1, F0 - c) and np.array_equal(G1, G0 + c)
+    assert np.array_equal(p0, p1) and np.array_equal(g0, g1)
+
+
 # past 28 bits from the second stage on, where p doubles (4 G stays within the
 # 2^30 of the padding columns' exponent)
 @pytest.mark.parametrize("c", [3 << 25, -(3 << 25), (1 << 27) - 9])
