@@ -66,7 +66,8 @@ sk_status plan_real(sk_ctx *ctx, Bump &bump, const float *W, int32_t n, const sk
         return fail(ctx, SK_ENOMEM, "arena too small for the instance (n=%d)", n);
     B.h_insts[0].wref = hi;
     B.h_insts[0].pscale = pscale;
-    return finish_tables(ctx, bump, B);
+    if ((st = finish_tables(ctx, bump, B)) == SK_OK) take_resident(bump, B);
+    return st;
 }
 
 }  // namespace
@@ -168,9 +169,14 @@ sk_status sk_solve_real(sk_ctx *ctx, const float *W, int32_t n, const sk_params 
         sk_report rep;
         memset(&rep, 0, sizeof rep);
         fill_report(c, &rep);
-        Bump rest = bump;
-        int64_t *d_rp = rest.take<int64_t>((size_t)n + 1);
-        int32_t *d_hint = rest.take<int32_t>((size_t)n);
+        Bump rest = rest_of(bump, B);
+        int64_t *d_rp = nullptr;
+        int32_t *d_hint = nullptr;
+        do {
+            rest.off = bump.off;
+            d_rp = rest.take<int64_t>((size_t)n + 1);
+            d_hint = rest.take<int32_t>((size_t)n);
+        } while (!(d_rp && d_hint) && release_resident(B, rest));
         if (!d_rp || !d_hint) return fail(ctx, SK_ENOMEM, "arena too small for the reduced matrix");
         double t = params->threshold;
         std::vector<int64_t> rp((size_t)n + 1);
@@ -204,9 +210,13 @@ sk_status sk_solve_real(sk_ctx *ctx, const float *W, int32_t n, const sk_params 
             HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
             report_from_check(ctx->h_checkout, pe, &rep, n, wref);
             nnz = ctx->h_nnz[0];
-            Bump tmp = rest;
-            int32_t *d_col = tmp.take<int32_t>((size_t)std::max<int64_t>(nnz, 1));
-            float *d_w = tmp.take<float>((size_t)std::max<int64_t>(nnz, 1));
+            int32_t *d_col = nullptr;
+            float *d_w = nullptr;
+            do {
+                Bump tmp = rest;
+                d_col = tmp.take<int32_t>((size_t)std::max<int64_t>(nnz, 1));
+                d_w = tmp.take<float>((size_t)std::max<int64_t>(nnz, 1));
+            } while (!(d_col && d_w) && release_resident(B, rest));
             if (!d_col || !d_w)
                 return fail(ctx, SK_ENOMEM, "the reduced matrix keeps %lld entries; the arena cannot hold them",
                             (long long)nnz);

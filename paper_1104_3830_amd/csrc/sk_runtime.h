@@ -42,6 +42,7 @@ struct Batch {
     int nmid = 0, mid_wide = 0;     // instances of k_mid; units of those with n > 512 (first in h_mid)
     bool mid_fold = false;          // launch_mid_pair's fold
     bool coop = false;              // one instance of k_mid's sizes that iterates in resident launches
+    size_t reserved = 0;            // bytes at the arena's end that those take
     int small_class[kSmallClasses] = {};  // of the latter, those with 64 c < n <= 64 (c + 1)
     int sweep_nmax = 0;  // largest n of the former
     std::vector<Inst> h_insts;
@@ -199,6 +200,12 @@ sk_status status_of(const Ctl &c);  // SK_OK, SK_ENOCONV (a stage capped) or SK_
 bool carve_instance(Bump &bump, const int16_t *W, int64_t pitch, int32_t n, const sk_params *prm,
                     Inst &I, const float *Wr = nullptr);
 sk_status finish_tables(sk_ctx *ctx, Bump &bump, Batch &B);
+// The resident iteration's area at the end of the arena, if there is room;
+// what a caller takes from the arena beside it (rest_of), and the area given
+// up for that (false: there is none).
+void take_resident(const Bump &bump, Batch &B);
+inline Bump rest_of(const Bump &bump, const Batch &B) { return Bump{bump.base, bump.cap - B.reserved, bump.off}; }
+bool release_resident(Batch &B, Bump &rest);
 sk_status plan_batch(sk_ctx *ctx, Bump &bump, int count, const int16_t *const *W,
                      const int64_t *pitch, const int32_t *n, const sk_params *prm, Batch &B);
 sk_status upload_batch(sk_ctx *ctx, Batch &B);

@@ -612,24 +612,6 @@ sk_status sk::finish_tables(sk_ctx *ctx, Bump &bump, Batch &B) {
         chk_used += chk;
     }
     B.chk_end.push_back(B.count);
-    // one instance: the exchange area of the resident iteration. Its room is
-    // that of the single-pass slots in sk_arena_bytes; where the caller's
-    // arena lacks it, the instance takes a launch per iteration, with the same
-    // results.
-    B.coop = false;
-    const auto resident = [](const Inst &I) { return I.mid || (I.Wr && I.n <= kMidN && I.deform_a <= 0.0); };
-    if (B.count == 1 && resident(B.h_insts[0])) {
-        Inst &I0 = B.h_insts[0];
-        Bump b2 = bump;
-        if (I0.Wr) {
-            I0.ctl2 = b2.take<Ctl>(1);
-            I0.G2 = b2.take<int32_t>(I0.n);
-            I0.gam2 = b2.take<float>(I0.n);
-        }
-        I0.coop = b2.take<char>(coop_bytes(I0.n));
-        B.coop = I0.ctl2 && I0.G2 && I0.gam2 && I0.coop;
-        if (B.coop) bump = b2;
-    }
     // grids: row sweep stages pad8(n) columns of potentials (8 B each) in LDS
     // (above kLdsMaxN it reads them from the instance's packed buffer)
     const size_t lds = B.nmax > kLdsMaxN ? 0 : sizeof(float2) * (size_t)pad8(B.nmax);
@@ -680,6 +662,41 @@ sk_status sk::finish_tables(sk_ctx *ctx, Bump &bump, Batch &B) {
     return SK_OK;
 }
 
+// The exchange area of the resident iteration (one instance), and for
+// real-valued weights the second copies it needs: at the arena's end, and only
+// if what is left has the room. Where it has not, or where the reduced matrix
+// needs the room later (release_resident), the instance takes a launch per
+// iteration, an int16 one with the same results.
+void sk::take_resident(const Bump &bump, Batch &B) {
+    B.coop = false;
+    B.reserved = 0;
+    if (B.count != 1) return;
+    Inst &I = B.h_insts[0];
+    if (!I.mid && !(I.Wr && I.n <= kMidN && I.deform_a <= 0.0)) return;
+    const size_t copies = I.Wr ? align_up(sizeof(Ctl), 256) + 2 * align_up(sizeof(float) * (size_t)I.n, 256) : 0;
+    const size_t bytes = align_up(coop_bytes(I.n), 256) + copies;
+    if (align_up(bump.off, 256) + bytes > bump.cap) return;
+    const size_t at = (bump.cap - bytes) / 256 * 256;
+    if (at < bump.off) return;
+    Bump area{bump.base, bump.cap, at};
+    if (I.Wr) {
+        I.ctl2 = area.take<Ctl>(1);
+        I.G2 = area.take<int32_t>(I.n);
+        I.gam2 = area.take<float>(I.n);
+    }
+    I.coop = area.take<char>(coop_bytes(I.n));
+    B.reserved = bump.cap - at;
+    B.coop = true;
+}
+
+bool sk::release_resident(Batch &B, Bump &rest) {
+    if (B.reserved == 0) return false;
+    rest.cap += B.reserved;
+    B.reserved = 0;
+    B.coop = false;
+    return true;
+}
+
 sk_status sk::plan_batch(sk_ctx *ctx, Bump &bump, int count, const int16_t *const *W,
                          const int64_t *pitch, const int32_t *n, const sk_params *prm,
                          Batch &B) {
@@ -687,7 +704,9 @@ sk_status sk::plan_batch(sk_ctx *ctx, Bump &bump, int count, const int16_t *cons
     for (int k = 0; k < count; ++k)
         if (!carve_instance(bump, W[k], pitch[k], n[k], prm, B.h_insts[k]))
             return fail(ctx, SK_ENOMEM, "arena too small for instance %d (n=%d)", k, n[k]);
-    return finish_tables(ctx, bump, B);
+    const sk_status st = finish_tables(ctx, bump, B);
+    if (st == SK_OK) take_resident(bump, B);
+    return st;
 }
 
 sk_status sk::upload_batch(sk_ctx *ctx, Batch &B) {

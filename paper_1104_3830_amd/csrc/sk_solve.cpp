@@ -73,9 +73,13 @@ sk_status reduce_and_solve(sk_ctx *ctx, Batch &B, Bump &rest, int64_t *d_rp, con
     int32_t *col = reinterpret_cast<int32_t *>(ctx->h_csr + o_col);
     int16_t *w = reinterpret_cast<int16_t *>(ctx->h_csr + o_w);
     if (nnz > 0) {
-        Bump tmp = rest;  // the entries are scratch until copied out
-        int32_t *d_col = tmp.take<int32_t>((size_t)nnz);
-        int16_t *d_w = tmp.take<int16_t>((size_t)nnz);
+        int32_t *d_col = nullptr;
+        int16_t *d_w = nullptr;
+        do {
+            Bump tmp = rest;  // the entries are scratch until copied out
+            d_col = tmp.take<int32_t>((size_t)nnz);
+            d_w = tmp.take<int16_t>((size_t)nnz);
+        } while (!(d_col && d_w) && release_resident(B, rest));
         if (!d_col || !d_w)
             return fail(ctx, SK_ENOMEM, "the reduced matrix keeps %lld entries; the arena cannot hold them",
                         (long long)nnz);
@@ -161,9 +165,14 @@ extern "C" sk_status sk_solve(sk_ctx *ctx, const int16_t *W, int32_t n, const sk
         StageResult r;
         r.p = c.p;
         fill_report(c, &r.rep);
-        Bump rest = bump;
-        int64_t *d_rp = rest.take<int64_t>((size_t)n + 1);
-        int32_t *d_hint = rest.take<int32_t>((size_t)n);
+        Bump rest = rest_of(bump, B);
+        int64_t *d_rp = nullptr;
+        int32_t *d_hint = nullptr;
+        do {
+            rest.off = bump.off;
+            d_rp = rest.take<int64_t>((size_t)n + 1);
+            d_hint = rest.take<int32_t>((size_t)n);
+        } while (!(d_rp && d_hint) && release_resident(B, rest));
         if (!d_rp || !d_hint)
             return fail(ctx, SK_ENOMEM, "arena too small for the reduced matrix (row pointers)");
         // FP64 certificate, row lengths of B at t and their scan: one sync
