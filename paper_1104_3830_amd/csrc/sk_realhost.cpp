@@ -26,7 +26,8 @@ size_t real_shared_extra(int32_t n, int64_t max_kept) {
 
 // Argument checks, the range scan (NaN / +inf rejected, the prescaling
 // factor and the common shift wref) and the plan of the one instance.
-sk_status plan_real(sk_ctx *ctx, Bump &bump, const float *W, int32_t n, const sk_params *params, Batch &B) {
+sk_status plan_real(sk_ctx *ctx, Bump &bump, const float *W, int32_t n, const sk_params *params, Batch &B,
+                    bool solve = false) {
     sk_status st = check_params(ctx, params, true);
     if (st != SK_OK) return st;
     if (!W) return fail(ctx, SK_EINVAL, "null W");
@@ -61,12 +62,19 @@ sk_status plan_real(sk_ctx *ctx, Bump &bump, const float *W, int32_t n, const sk
         return fail(ctx, SK_EINVAL, "p * (w_max - w_min) = %g exceeds 1e8", (double)pmax * pscale * range);
     const int64_t pitch = n;
     const int16_t *Ws[1] = {nullptr};
-    B.h_insts.assign(1, Inst{});
-    if (!carve_instance(bump, Ws[0], pitch, n, params, B.h_insts[0], W))
-        return fail(ctx, SK_ENOMEM, "arena too small for the instance (n=%d)", n);
-    B.h_insts[0].wref = hi;
-    B.h_insts[0].pscale = pscale;
-    if ((st = finish_tables(ctx, bump, B)) == SK_OK) take_resident(bump, B);
+    for (int lean = 0; lean < 2; ++lean) {
+        Bump b = bump;
+        B.h_insts.assign(1, Inst{});
+        if (!carve_instance(b, Ws[0], pitch, n, params, B.h_insts[0], W, false, false))
+            return fail(ctx, SK_ENOMEM, "arena too small for the instance (n=%d)", n);
+        B.h_insts[0].wref = hi;
+        B.h_insts[0].pscale = pscale;
+        if ((st = finish_tables(ctx, b, B, lean != 0, solve)) == SK_OK) {
+            bump = b;
+            take_resident(bump, B);
+        }
+        if (st != SK_ENOMEM) break;
+    }
     return st;
 }
 
@@ -80,7 +88,7 @@ size_t sk_real_arena_bytes(int32_t n, int64_t max_kept) {
     // up to kMidN the resident iteration's exchange area and second copies
     const size_t coop = n > kMidN ? 0 : align_up(coop_bytes(n), 256) + align_up(sizeof(Ctl), 256) +
                                             2 * align_up(sizeof(float) * (size_t)n, 256);
-    return instance_bytes(n, 1, SK_W_I16) + shared_bytes(1, &n) + real_shared_extra(n, max_kept) + coop + 4096;
+    return instance_bytes(n, 1, SK_W_I16, 0, 0) + shared_bytes(1, &n) + real_shared_extra(n, max_kept) + coop + 4096;
 }
 
 sk_status sk_scale_real(sk_ctx *ctx, const float *W, int32_t n, const sk_params *params,
@@ -139,7 +147,7 @@ sk_status sk_solve_real(sk_ctx *ctx, const float *W, int32_t n, const sk_params 
     ctx->absorbs = 0;
     Bump bump{ctx->arena, ctx->arena_bytes};
     Batch &B = ctx->scratch_batch;
-    sk_status st = plan_real(ctx, bump, W, n, params, B);
+    sk_status st = plan_real(ctx, bump, W, n, params, B, true);
     if (st != SK_OK) return st;
     const bool adaptive = params->opt_ratio >= 1.0;
     const double log_ratio = adaptive ? std::log(params->opt_ratio) : 0.0;
@@ -170,14 +178,8 @@ sk_status sk_solve_real(sk_ctx *ctx, const float *W, int32_t n, const sk_params 
         memset(&rep, 0, sizeof rep);
         fill_report(c, &rep);
         Bump rest = rest_of(bump, B);
-        int64_t *d_rp = nullptr;
-        int32_t *d_hint = nullptr;
-        do {
-            rest.off = bump.off;
-            d_rp = rest.take<int64_t>((size_t)n + 1);
-            d_hint = rest.take<int32_t>((size_t)n);
-        } while (!(d_rp && d_hint) && release_resident(B, rest));
-        if (!d_rp || !d_hint) return fail(ctx, SK_ENOMEM, "arena too small for the reduced matrix");
+        int64_t *d_rp = B.d_rp;
+        int32_t *d_hint = B.d_hint;
         double t = params->threshold;
         std::vector<int64_t> rp((size_t)n + 1);
         std::vector<int32_t> hint((size_t)n), colh;
@@ -216,7 +218,7 @@ sk_status sk_solve_real(sk_ctx *ctx, const float *W, int32_t n, const sk_params 
                 Bump tmp = rest;
                 d_col = tmp.take<int32_t>((size_t)std::max<int64_t>(nnz, 1));
                 d_w = tmp.take<float>((size_t)std::max<int64_t>(nnz, 1));
-            } while (!(d_col && d_w) && release_resident(B, rest));
+            } while (!(d_col && d_w) && more_room(B, rest));
             if (!d_col || !d_w)
                 return fail(ctx, SK_ENOMEM, "the reduced matrix keeps %lld entries; the arena cannot hold them",
                             (long long)nnz);

@@ -18,7 +18,8 @@ struct TilePlan {
     int tile_cols, ntiles, seg_rows, nseg;
 };
 TilePlan plan_tiles(int32_t n, int vec8);
-size_t instance_bytes(int32_t n, int vec8, int storage, int fused = 0);
+// mid: with what k_mid needs, where n is of its sizes (carve_instance's mid_ok)
+size_t instance_bytes(int32_t n, int vec8, int storage, int fused = 0, int mid = 1);
 size_t shared_bytes(int32_t count, const int32_t *n);
 size_t pad_copy_bytes(int32_t n);
 // LDS of the kernels that stage (G_j, gam_j) per column (FP64 check,
@@ -43,6 +44,11 @@ struct Batch {
     bool mid_fold = false;          // launch_mid_pair's fold
     bool coop = false;              // one instance of k_mid's sizes that iterates in resident launches
     size_t reserved = 0;            // bytes at the arena's end that those take
+    // one instance: where its scratch and the FP64 check's begins, the last
+    // of the plan; a solve's row pointers and hints
+    size_t scratch_at = 0;
+    int64_t *d_rp = nullptr;
+    int32_t *d_hint = nullptr;
     int small_class[kSmallClasses] = {};  // of the latter, those with 64 c < n <= 64 (c + 1)
     int sweep_nmax = 0;  // largest n of the former
     std::vector<Inst> h_insts;
@@ -198,16 +204,20 @@ sk_status check_range(sk_ctx *ctx, const sk_params *prm);  // p small enough for
 sk_status status_of(const Ctl &c);  // SK_OK, SK_ENOCONV (a stage capped) or SK_ENOSUPPORT
 // Wr != nullptr: a real-valued instance (W unused; Wr read with pitch `pitch`).
 bool carve_instance(Bump &bump, const int16_t *W, int64_t pitch, int32_t n, const sk_params *prm,
-                    Inst &I, const float *Wr = nullptr);
-sk_status finish_tables(sk_ctx *ctx, Bump &bump, Batch &B);
+                    Inst &I, const float *Wr = nullptr, bool mid_ok = true, bool scratch = true);
+// lean: the FP64 check on the sweeps' row segments, an instance at a time.
+// The scratch of an instance carved without it (one alone) comes last, and
+// before it, for a solve, the reduced matrix's row pointers and hints.
+sk_status finish_tables(sk_ctx *ctx, Bump &bump, Batch &B, bool lean = false, bool solve = false);
 // The resident iteration's area at the end of the arena, if there is room;
-// what a caller takes from the arena beside it (rest_of), and the area given
-// up for that (false: there is none).
+// what a caller takes from the arena beside it (rest_of), and where that is
+// too little between two stages (more_room; false: there is no more): the
+// scratch, then that area, whose iteration then goes on launch by launch.
 void take_resident(const Bump &bump, Batch &B);
 inline Bump rest_of(const Bump &bump, const Batch &B) { return Bump{bump.base, bump.cap - B.reserved, bump.off}; }
-bool release_resident(Batch &B, Bump &rest);
+bool more_room(Batch &B, Bump &rest);
 sk_status plan_batch(sk_ctx *ctx, Bump &bump, int count, const int16_t *const *W,
-                     const int64_t *pitch, const int32_t *n, const sk_params *prm, Batch &B);
+                     const int64_t *pitch, const int32_t *n, const sk_params *prm, Batch &B, bool solve = false);
 sk_status upload_batch(sk_ctx *ctx, Batch &B);
 sk_status start_batch(sk_ctx *ctx, Batch &B, const sk_params *prm, void *const *pot_in);
 sk_status read_ctl(sk_ctx *ctx, Batch &B);

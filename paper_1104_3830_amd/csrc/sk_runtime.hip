@@ -47,24 +47,23 @@ TilePlan plan_tiles(int32_t n, int vec8) {
 static bool mid_size(int32_t n) { return n > kSmallN && n <= kMidN; }
 static size_t mid_slots(int32_t n) { return 2 * (size_t)((n + kMidRows - 1) / kMidRows); }
 
-size_t instance_bytes(int32_t n, int vec8, int storage, int fused) {
+size_t instance_bytes(int32_t n, int vec8, int storage, int fused, int mid) {
     TilePlan t = plan_tiles(n, vec8);
+    const bool kstore = storage == SK_K_BF16 || storage == SK_K_F32;
+    const bool is_mid = mid && mid_size(n) && !kstore;
     size_t b = 0;
     b += align_up(sizeof(int32_t) * n, 256) * 3;  // F[2], G
     b += align_up(sizeof(float) * n, 256) * 3;    // phi[2], gam
     const size_t slots = fused ? std::max(t.nseg, kFusedSlots) : t.nseg;
-    b += align_up(sizeof(float) * slots * n, 256);
+    b += align_up(sizeof(float) * std::max(slots * n, is_mid ? mid_slots(n) * pad8(n) : 0), 256);
     b += align_up(sizeof(uint32_t) * n, 256);
     b += align_up(sizeof(Ctl), 256);
     b += align_up(sizeof(float) * std::max((n + kRowWaves - 1) / kRowWaves, kFusedSlots), 256) * 2;
     b += align_up(sizeof(float) * n, 256);  // rres
     b += align_up(sizeof(uint32_t) * kRowResSlots * kRowResStride, 256);  // rowres
     if (n > kLdsMaxN) b += align_up(8 * (size_t)pad8(n), 256);  // colpack
-    if (mid_size(n) && storage == SK_W_I16) {
-        b += align_up(sizeof(float) * mid_slots(n) * pad8(n), 256);
-        b += align_up(sizeof(Ctl), 256) + align_up(sizeof(int32_t) * n, 256) + align_up(sizeof(float) * n, 256);
-    }
-    if (storage == SK_K_BF16 || storage == SK_K_F32) {
+    if (is_mid) b += align_up(sizeof(Ctl), 256) + align_up(sizeof(int32_t) * n, 256) + align_up(sizeof(float) * n, 256);
+    if (kstore) {
         const size_t es = storage == SK_K_BF16 ? 2 : 4;
         const size_t kp = (size_t)(n + 7) / 8 * 8;
         b += align_up(es * (size_t)n * kp, 256);
@@ -383,9 +382,23 @@ sk_status sk::check_params(sk_ctx *ctx, const sk_params *p, bool real) {
 
 // ---------------------------------------------------------------- batch plan
 
+// What an iteration leaves behind and the next stage does not read: the column
+// partials, and k_mid's second copies.
+static bool carve_scratch(Bump &bump, Inst &I) {
+    const size_t nn = (size_t)I.n;
+    const size_t slots = I.fused ? std::max(I.nseg, kFusedSlots) : I.nseg;
+    I.colpart = bump.take<float>(I.mid ? mid_slots(I.n) * pad8(I.n) : slots * nn);
+    if (!I.colpart) return false;
+    if (!I.mid) return true;
+    I.ctl2 = bump.take<Ctl>(1);
+    I.G2 = bump.take<int32_t>(nn);
+    I.gam2 = bump.take<float>(nn);
+    return I.ctl2 && I.G2 && I.gam2;
+}
+
 // Fills the descriptor of one instance and carves its buffers from `bump`.
 bool sk::carve_instance(Bump &bump, const int16_t *W, int64_t pitch, int32_t nn,
-                        const sk_params *prm, Inst &I, const float *Wr) {
+                        const sk_params *prm, Inst &I, const float *Wr, bool mid_ok, bool scratch) {
     I = Inst{};
     I.W = W;
     I.pitch = pitch;
@@ -420,8 +433,6 @@ bool sk::carve_instance(Bump &bump, const int16_t *W, int64_t pitch, int32_t nn,
     I.seg_rows = t.seg_rows;
     I.ntiles = t.ntiles;
     I.tile_cols = t.tile_cols;
-    I.chk_seg = check_seg_rows(nn, t);
-    I.chk_nseg = check_segs(nn, t);
     I.n_p = prm->n_p;
     for (int s = 0; s < prm->n_p; ++s) I.ladder[s] = prm->p_ladder[s];
     I.tol = (float)prm->tol;
@@ -430,43 +441,39 @@ bool sk::carve_instance(Bump &bump, const int16_t *W, int64_t pitch, int32_t nn,
     I.fused = prm->fused ? 1 : 0;
     I.deform_a = prm->deform_a > 0.0 ? prm->deform_a : 0.0;
     I.fused_grid = std::min(kFusedSlots, std::max(1, nn / 2));
-    // by size and options alone, so that a result does not depend on what
-    // else is in the batch (the deformed iteration moves p, and with it every
-    // entry, each time: it stays with the sweeps)
+    // by size and options, so that a result does not depend on what else is in
+    // the batch (the deformed iteration moves p, and with it every entry, each
+    // time: it stays with the sweeps). Only an arena without the room for
+    // k_mid's column partials (64 floats per column at n = 1024, where the
+    // sweeps need 8 or fewer) leaves its sizes to the sweeps: !mid_ok.
     const bool onchip = !Wr && prm->storage == SK_W_I16 && !prm->fused && prm->method == SK_SINKHORN &&
                         I.deform_a <= 0.0;
     I.small = onchip && nn <= kSmallN;
-    I.mid = onchip && mid_size(nn);
+    I.mid = onchip && mid_ok && mid_size(nn);
     for (int b = 0; b < 2; ++b) {
         I.F[b] = bump.take<int32_t>(nn);
         I.phi[b] = bump.take<float>(nn);
     }
     I.G = bump.take<int32_t>(nn);
     I.gam = bump.take<float>(nn);
-    const size_t slots = I.fused ? std::max(t.nseg, kFusedSlots) : t.nseg;
-    I.colpart = bump.take<float>(I.mid ? mid_slots(nn) * pad8(nn) : slots * nn);
+    if (scratch && !carve_scratch(bump, I)) return false;
     I.rescue = bump.take<uint32_t>(nn);
     I.ctl = bump.take<Ctl>(1);
     const int nrows_units = (nn + kRowWaves - 1) / kRowWaves;
     I.ncolslots = I.fused ? I.fused_grid : t.nseg;
     I.res_slots = bump.take<float>(std::max(nrows_units, kFusedSlots));
-    I.drift_slots = bump.take<float>(std::max(nrows_units, kFusedSlots));
+    if (prm->storage != SK_W_I16) {
+        I.drift_slots = bump.take<float>(std::max(nrows_units, kFusedSlots));
+        if (!I.drift_slots) return false;
+    }
     I.rres = bump.take<float>(nn);
     I.rowres = bump.take<uint32_t>((size_t)kRowResSlots * kRowResStride);
-    if (!I.res_slots || !I.drift_slots || !I.rres || !I.rowres) return false;
+    if (!I.res_slots || !I.rres || !I.rowres) return false;
     if (nn > kLdsMaxN && !Wr) {
         I.colpack = bump.take<int2>((size_t)pad8(nn));
         if (!I.colpack) return false;
     }
-    if (!I.F[0] || !I.F[1] || !I.phi[0] || !I.phi[1] || !I.G || !I.gam || !I.colpart ||
-        !I.rescue || !I.ctl)
-        return false;
-    if (I.mid) {
-        I.ctl2 = bump.take<Ctl>(1);
-        I.G2 = bump.take<int32_t>(nn);
-        I.gam2 = bump.take<float>(nn);
-        if (!I.ctl2 || !I.G2 || !I.gam2) return false;
-    }
+    if (!I.F[0] || !I.F[1] || !I.phi[0] || !I.phi[1] || !I.G || !I.gam || !I.rescue || !I.ctl) return false;
     I.kpitch = (nn + 7) / 8 * 8;
     if (prm->storage != SK_W_I16) {
         const size_t es = prm->storage == SK_K_BF16 ? 2 : 4;
@@ -480,7 +487,7 @@ bool sk::carve_instance(Bump &bump, const int16_t *W, int64_t pitch, int32_t nn,
 }
 
 // Work-unit tables, shared scratch and launch grids for the instances in B.h_insts.
-sk_status sk::finish_tables(sk_ctx *ctx, Bump &bump, Batch &B) {
+sk_status sk::finish_tables(sk_ctx *ctx, Bump &bump, Batch &B, bool lean, bool solve) {
     B.count = (int)B.h_insts.size();
     // matrix loads take the non-temporal hint only when the batch's matrices
     // cannot stay in the last-level cache between passes
@@ -523,7 +530,10 @@ sk_status sk::finish_tables(sk_ctx *ctx, Bump &bump, Batch &B) {
     size_t chk_max = 0, chk_sum = 0;
     for (int q = 0; q < B.count; ++q) {
         const int k = B.order[q];
-        const Inst &I = B.h_insts[k];
+        Inst &I = B.h_insts[k];
+        const TilePlan t{I.tile_cols, I.ntiles, I.seg_rows, I.nseg};
+        I.chk_seg = lean ? I.seg_rows : check_seg_rows(I.n, t);
+        I.chk_nseg = lean ? I.nseg : check_segs(I.n, t);
         if (q == B.nsweep) {
             B.nsweep_rows = (int)B.h_rows.size();
             B.nsweep_fins = (int)B.h_fins.size();
@@ -534,7 +544,7 @@ sk_status sk::finish_tables(sk_ctx *ctx, Bump &bump, Batch &B) {
         B.fin_at[q] = (int)B.h_fins.size();
         for (int r = 0; r < I.n; r += kRowWaves) B.h_rows.push_back(RowUnit{k, r});
         for (int g = 0; g * kFinCols < I.n; ++g) B.h_fins.push_back(FinUnit{k, g});
-        if (B.count > 1)
+        if (B.count > 1 && !lean)
             for (int s = 0; s < I.chk_nseg; ++s)
                 for (int tt = 0; tt * kColTile8 < I.n; ++tt) B.h_ccols.push_back(ColUnit{k, tt, s, 0});
         const size_t chk = check_doubles(I.n, std::max(I.chk_nseg, I.nseg));
@@ -585,33 +595,14 @@ sk_status sk::finish_tables(sk_ctx *ctx, Bump &bump, Batch &B) {
     B.d_rows = bump.take<RowUnit>(B.h_rows.size());
     B.d_cols = bump.take<ColUnit>(B.h_cols.size());
     B.d_fins = bump.take<FinUnit>(B.h_fins.size());
-    B.d_mid = B.h_mid.empty() ? nullptr : bump.take<RowUnit>(B.h_mid.size());
+    B.d_mid = nullptr;  // (an instance alone needs none)
+    if (B.count > 1 && !B.h_mid.empty() && !(B.d_mid = bump.take<RowUnit>(B.h_mid.size())))
+        return fail(ctx, SK_ENOMEM, "arena too small for the batch tables");
     B.d_counts = bump.take<int64_t>(B.nmax + 1);
     B.d_ccols = B.h_ccols.empty() ? nullptr : bump.take<ColUnit>(B.h_ccols.size());
-    if ((!B.h_mid.empty() && !B.d_mid) || (!B.h_ccols.empty() && !B.d_ccols) || !B.d_insts || !B.d_rows || !B.d_cols ||
+    if ((!B.h_ccols.empty() && !B.d_ccols) || !B.d_insts || !B.d_rows || !B.d_cols ||
         !B.d_fins || !B.d_counts || !B.d_ctl_all || !B.d_checkout || !B.d_nnz)
         return fail(ctx, SK_ENOMEM, "arena too small for the batch tables");
-    // the check's scratch: consecutive instances share it group by group
-    size_t chk_cap = check_scratch(chk_max, chk_sum);
-    B.d_chk = bump.take<double>(chk_cap);
-    if (!B.d_chk) {
-        chk_cap = chk_max;
-        B.d_chk = bump.take<double>(chk_cap);
-    }
-    if (!B.d_chk) return fail(ctx, SK_ENOMEM, "arena too small for the batch tables");
-    B.chk_end.clear();
-    size_t chk_used = 0;
-    for (int q = 0; q < B.count; ++q) {
-        Inst &I = B.h_insts[B.order[q]];
-        const size_t chk = check_doubles(I.n, std::max(I.chk_nseg, I.nseg));
-        if (chk_used + chk > chk_cap) {
-            B.chk_end.push_back(q);
-            chk_used = 0;
-        }
-        I.chk = B.d_chk + chk_used;
-        chk_used += chk;
-    }
-    B.chk_end.push_back(B.count);
     // grids: row sweep stages pad8(n) columns of potentials (8 B each) in LDS
     // (above kLdsMaxN it reads them from the instance's packed buffer)
     const size_t lds = B.nmax > kLdsMaxN ? 0 : sizeof(float2) * (size_t)pad8(B.nmax);
@@ -658,6 +649,35 @@ sk_status sk::finish_tables(sk_ctx *ctx, Bump &bump, Batch &B) {
         B.d_row_bounds = bump.take<int32_t>((size_t)g + 1);
         if (!B.d_row_bounds) return fail(ctx, SK_ENOMEM, "arena too small for the batch tables");
     }
+    if (solve) {
+        B.d_rp = bump.take<int64_t>((size_t)B.nmax + 1);
+        B.d_hint = bump.take<int32_t>((size_t)B.nmax);
+        if (!B.d_rp || !B.d_hint) return fail(ctx, SK_ENOMEM, "arena too small for the reduced matrix (row pointers)");
+    }
+    B.scratch_at = align_up(bump.off, 256);
+    if (!B.h_insts[0].colpart && !carve_scratch(bump, B.h_insts[0]))
+        return fail(ctx, SK_ENOMEM, "arena too small for the column partials");
+    // the check's scratch: consecutive instances share it group by group
+    size_t chk_cap = lean ? chk_max : check_scratch(chk_max, chk_sum);
+    B.d_chk = bump.take<double>(chk_cap);
+    if (!B.d_chk) {
+        chk_cap = chk_max;
+        B.d_chk = bump.take<double>(chk_cap);
+    }
+    if (!B.d_chk) return fail(ctx, SK_ENOMEM, "arena too small for the batch tables");
+    B.chk_end.clear();
+    size_t chk_used = 0;
+    for (int q = 0; q < B.count; ++q) {
+        Inst &I = B.h_insts[B.order[q]];
+        const size_t chk = check_doubles(I.n, std::max(I.chk_nseg, I.nseg));
+        if (chk_used + chk > chk_cap || (lean && q > 0)) {
+            B.chk_end.push_back(q);
+            chk_used = 0;
+        }
+        I.chk = B.d_chk + chk_used;
+        chk_used += chk;
+    }
+    B.chk_end.push_back(B.count);
     B.col_grid = (int)std::max<size_t>(1, std::min<size_t>(B.h_cols.size(), (size_t)ctx->num_cus * 8));
     return SK_OK;
 }
@@ -665,8 +685,8 @@ sk_status sk::finish_tables(sk_ctx *ctx, Bump &bump, Batch &B) {
 // The exchange area of the resident iteration (one instance), and for
 // real-valued weights the second copies it needs: at the arena's end, and only
 // if what is left has the room. Where it has not, or where the reduced matrix
-// needs the room later (release_resident), the instance takes a launch per
-// iteration, an int16 one with the same results.
+// needs the room later (more_room), the instance takes a launch per iteration,
+// an int16 one with the same results.
 void sk::take_resident(const Bump &bump, Batch &B) {
     B.coop = false;
     B.reserved = 0;
@@ -689,7 +709,11 @@ void sk::take_resident(const Bump &bump, Batch &B) {
     B.coop = true;
 }
 
-bool sk::release_resident(Batch &B, Bump &rest) {
+bool sk::more_room(Batch &B, Bump &rest) {
+    if (B.scratch_at != 0 && rest.off > B.scratch_at) {
+        rest.off = B.scratch_at;
+        return true;
+    }
     if (B.reserved == 0) return false;
     rest.cap += B.reserved;
     B.reserved = 0;
@@ -699,13 +723,26 @@ bool sk::release_resident(Batch &B, Bump &rest) {
 
 sk_status sk::plan_batch(sk_ctx *ctx, Bump &bump, int count, const int16_t *const *W,
                          const int64_t *pitch, const int32_t *n, const sk_params *prm,
-                         Batch &B) {
-    B.h_insts.assign(count, Inst{});
-    for (int k = 0; k < count; ++k)
-        if (!carve_instance(bump, W[k], pitch[k], n[k], prm, B.h_insts[k]))
-            return fail(ctx, SK_ENOMEM, "arena too small for instance %d (n=%d)", k, n[k]);
-    const sk_status st = finish_tables(ctx, bump, B);
-    if (st == SK_OK) take_resident(bump, B);
+                         Batch &B, bool solve) {
+    // an arena without the room for all of it: what the sweeps need, of the
+    // batch tables the least. Newton's vectors follow the plan, which
+    // leaves them as much as there can be.
+    const bool one = count == 1, newton = prm->method == SK_NEWTON;
+    sk_status st = SK_ENOMEM;
+    for (int lean = newton ? 1 : 0; lean < 2; ++lean) {
+        Bump b = bump;
+        B.h_insts.assign(count, Inst{});
+        int k = 0;
+        while (k < count && carve_instance(b, W[k], pitch[k], n[k], prm, B.h_insts[k], nullptr, !lean, !one)) ++k;
+        st = k < count ? fail(ctx, SK_ENOMEM, "arena too small for instance %d (n=%d)", k, n[k])
+                       : finish_tables(ctx, b, B, lean != 0, solve);
+        if (st == SK_OK) {
+            bump = b;
+            take_resident(bump, B);
+            if (newton) B.scratch_at = 0;
+        }
+        if (st != SK_ENOMEM) break;
+    }
     return st;
 }
 
@@ -725,7 +762,7 @@ sk_status sk::upload_batch(sk_ctx *ctx, Batch &B) {
     if (B.nsweep > 0)
         HIPCHK(ctx, hipMemcpyAsync(B.d_cols, B.h_cols.data(), sizeof(ColUnit) * B.h_cols.size(),
                                    hipMemcpyHostToDevice, ctx->stream));
-    if (!B.h_mid.empty())
+    if (B.d_mid)
         HIPCHK(ctx, hipMemcpyAsync(B.d_mid, B.h_mid.data(), sizeof(RowUnit) * B.h_mid.size(),
                                    hipMemcpyHostToDevice, ctx->stream));
     bool pads = false;
@@ -985,11 +1022,12 @@ sk_status sk::enqueue_checks(sk_ctx *ctx, Batch &B) {
         HIPCHK(ctx, PROF(ctx, KID_CHECK_ROWS,
                          launch_check_rows(B.d_insts, B.d_rows + B.row_at[q0], nrows, grid, 1, 0.0, nullptr, nullptr,
                                            gq_lds_bytes(nmax), nt, 0, ctx->stream)));
-        const bool one = B.count == 1;
-        const int ncols = one ? (nmax + kColTile8 - 1) / kColTile8 * B.h_insts[0].chk_nseg
+        const bool one = B.h_ccols.empty();  // no table: the group is one instance
+        const int k0 = B.order[q0];
+        const int ncols = one ? (nmax + kColTile8 - 1) / kColTile8 * B.h_insts[k0].chk_nseg
                               : B.ccol_at[q1] - B.ccol_at[q0];
         HIPCHK(ctx, PROF(ctx, KID_CHECK_COLS,
-                         launch_check_cols(B.d_insts, one ? nullptr : B.d_ccols + B.ccol_at[q0], 0, ncols, 1, nt,
+                         launch_check_cols(B.d_insts, one ? nullptr : B.d_ccols + B.ccol_at[q0], k0, ncols, 1, nt,
                                            ctx->stream)));
         HIPCHK(ctx, launch_check_sums(B.d_insts, B.d_fins + B.fin_at[q0], 0, B.fin_at[q1] - B.fin_at[q0], q0, q1 - q0,
                                       1, B.d_checkout, ctx->stream));

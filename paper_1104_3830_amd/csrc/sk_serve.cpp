@@ -45,6 +45,7 @@ struct Request {
     size_t ring_off = 0;         // offset in the pinned ring
     bool in_ring = false;
     size_t off = 0, len = 0;     // device region in the arena
+    bool mid_ok = true;          // ... with what k_mid needs
     Inst inst{};
     bool loaded = false;         // W is in its device region
     bool copying = false;        // placed, and its copy from the ring is in flight (ev)
@@ -161,8 +162,8 @@ static void stage_rows(int16_t *dst, const int16_t *src, int32_t n) {
     for (auto &t : th) t.join();
 }
 
-static size_t footprint(int32_t n) {
-    return align_up(wbytes_of(n), 256) + instance_bytes(n, 1, SK_W_I16) + 4096;
+static size_t footprint(int32_t n, bool mid_ok) {
+    return align_up(wbytes_of(n), 256) + instance_bytes(n, 1, SK_W_I16, 0, mid_ok) + 4096;
 }
 
 // Carves the request's device region at offset `off` (W first, then the
@@ -171,7 +172,7 @@ static void place(Server *S, Request *r, size_t off) {
     r->off = off;
     Bump bump{S->ctx->arena + off, r->len};
     int16_t *dW = bump.take<int16_t>((size_t)r->n * pad8(r->n));
-    carve_instance(bump, dW, pad8(r->n), r->n, &r->prm, r->inst);
+    carve_instance(bump, dW, pad8(r->n), r->n, &r->prm, r->inst, nullptr, r->mid_ok);
 }
 
 // Marks r finished (caller holds S->mu) and records it for sk_completed; the
@@ -237,7 +238,12 @@ static sk_status rebuild(Server *S) {
     // the first part of the tables region holds the init-unit table
     S->d_init_units = tb.take<RowUnit>(kLdsMaxN / kRowWaves * 64);
     S->d_fresh = tb.take<int>(kMaxBatch);
+    const Bump start = tb;
     sk_status st = finish_tables(ctx, tb, S->B);
+    if (st == SK_ENOMEM) {
+        tb = start;
+        st = finish_tables(ctx, tb, S->B, true);
+    }
     if (st != SK_OK) return st;
     return upload_batch(ctx, S->B);
 }
@@ -560,13 +566,16 @@ extern "C" sk_status sk_submit(sk_ctx *ctx, const int16_t *W_host, int32_t n, co
     std::lock_guard<std::mutex> call(ctx->mu);
     Server *S = ensure_server(ctx);
     if (!S) return fail(ctx, SK_EDEVICE, "could not start the serving thread");
-    const size_t len = footprint(n);
+    // an arena that only the sweeps' footprint fits takes the request with that
+    const bool mid_ok = footprint(n, true) + S->tables_len <= ctx->arena_bytes;
+    const size_t len = footprint(n, mid_ok);
     if (len + S->tables_len > ctx->arena_bytes)
         return fail(ctx, SK_ENOMEM, "n = %d can never fit in the arena", n);
     Request *r = new Request();
     r->n = n;
     r->prm = *params;
     r->len = len;
+    r->mid_ok = mid_ok;
     r->t_submit = std::chrono::steady_clock::now();
     const size_t wbytes = wbytes_of(n);
     // W goes to the pinned ring when it has room (a parallel host copy; the

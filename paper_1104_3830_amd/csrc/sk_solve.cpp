@@ -79,7 +79,7 @@ sk_status reduce_and_solve(sk_ctx *ctx, Batch &B, Bump &rest, int64_t *d_rp, con
             Bump tmp = rest;  // the entries are scratch until copied out
             d_col = tmp.take<int32_t>((size_t)nnz);
             d_w = tmp.take<int16_t>((size_t)nnz);
-        } while (!(d_col && d_w) && release_resident(B, rest));
+        } while (!(d_col && d_w) && more_room(B, rest));
         if (!d_col || !d_w)
             return fail(ctx, SK_ENOMEM, "the reduced matrix keeps %lld entries; the arena cannot hold them",
                         (long long)nnz);
@@ -149,7 +149,7 @@ extern "C" sk_status sk_solve(sk_ctx *ctx, const int16_t *W, int32_t n, const sk
     const bool adaptive = params->opt_ratio >= 1.0;
     const double log_ratio = adaptive ? std::log(params->opt_ratio) : 0.0;
     const bool kpath = params->storage != SK_W_I16;
-    if ((st = plan_batch(ctx, bump, 1, Ws, &pitch, &n, params, B)) != SK_OK) return st;
+    if ((st = plan_batch(ctx, bump, 1, Ws, &pitch, &n, params, B, true)) != SK_OK) return st;
     B.h_insts[0].pause = (adaptive && !kpath && params->method == SK_SINKHORN) ? 1 : 0;
     if ((st = upload_batch(ctx, B)) != SK_OK) return st;
     void *pots[1] = {potentials};
@@ -166,15 +166,8 @@ extern "C" sk_status sk_solve(sk_ctx *ctx, const int16_t *W, int32_t n, const sk
         r.p = c.p;
         fill_report(c, &r.rep);
         Bump rest = rest_of(bump, B);
-        int64_t *d_rp = nullptr;
-        int32_t *d_hint = nullptr;
-        do {
-            rest.off = bump.off;
-            d_rp = rest.take<int64_t>((size_t)n + 1);
-            d_hint = rest.take<int32_t>((size_t)n);
-        } while (!(d_rp && d_hint) && release_resident(B, rest));
-        if (!d_rp || !d_hint)
-            return fail(ctx, SK_ENOMEM, "arena too small for the reduced matrix (row pointers)");
+        int64_t *d_rp = B.d_rp;
+        int32_t *d_hint = B.d_hint;
         // FP64 certificate, row lengths of B at t and their scan: one sync
         double t = params->threshold;
         const CheckCounts cc{std::log(t), B.d_counts, d_hint};
