@@ -215,13 +215,36 @@ bool unique_within(int n, const int64_t *rp, const int32_t *col, const float *w,
     return queue.size() == (size_t)n;
 }
 
+// How far the weights of two perfect matchings can be from what their reduced
+// costs say: summed over the rows (a matching has one entry in each), the most
+// by which a reduced cost of the row can be below 0 and its matched one's off
+// 0, with the rounding of their two subtractions. It is found from the
+// potentials as they are, since it grows with them and not with the weights.
+double certificate_slack(int n, const int64_t *rp, const int32_t *col, const float *w, const Matching &M) {
+    constexpr double kHalfUlp = 0x1p-53;
+    double sum = 0.0;
+    for (int i = 0; i < n; ++i) {
+        double below = 0.0;
+        for (int64_t e = rp[i]; e < rp[i + 1]; ++e) {
+            const double c = -(double)w[e] - M.u[i], r = c - M.v[col[e]];
+            const double err = 2 * kHalfUlp * (std::fabs(c) + std::fabs(r));
+            below = std::max(below, err - r);
+            if (e == M.edge_of[i]) sum += std::fabs(r) + err;
+        }
+        sum += below;
+    }
+    return sum;
+}
+
 }  // namespace
 
 // Any start gives an optimal matching, and one that is unique is the same from
-// all. Where others come within kTieTol (of the largest |w|: far above the
-// rounding of the potentials, below a float32 step of the larger weights) the
-// choice would hang on the start, so the search is done again from potentials
-// 0, which decides there.
+// all. Where others come within kTieTol (of the largest |w|: below a float32
+// step of the larger weights) the choice would hang on the start, so the
+// search is done again from potentials 0, which decides there. So it is where
+// the potentials are so large beside the weights that their rounding takes
+// more than half of that (small weights kept of a matrix whose others are
+// not, a far start): then they neither prove the matching nor its uniqueness.
 sk_status solve_real_impl(int n, const int64_t *rp, const int32_t *col, const float *w, const int32_t *hint,
                           MatchStart *start, int32_t *perm, double *weight) {
     constexpr double kTieTol = 1e-9, kSlack = 1e-13;
@@ -236,12 +259,13 @@ sk_status solve_real_impl(int n, const int64_t *rp, const int32_t *col, const fl
         }
     }
     Matching M;
-    bool solved = false;
+    bool solved = false, exact = true;
     if (start) {
         M.v = start->v;
         const sk_status st = augment_all(n, rp, col, w, hint, start, kSlack * wmax, M);
         if (st != SK_OK) return st;
-        solved = unique_within(n, rp, col, w, M, kTieTol * wmax);
+        exact = certificate_slack(n, rp, col, w, M) <= 0.5 * kTieTol * wmax;
+        solved = exact && unique_within(n, rp, col, w, M, kTieTol * wmax);
         start->v = M.v;
         start->col = M.col_of;
     }
@@ -249,6 +273,10 @@ sk_status solve_real_impl(int n, const int64_t *rp, const int32_t *col, const fl
         M.v.assign((size_t)n, 0.0);
         const sk_status st = augment_all(n, rp, col, w, hint, nullptr, 0.0, M);
         if (st != SK_OK) return st;
+        if (!exact) {  // the next start is this one's optimum
+            start->v = M.v;
+            start->col = M.col_of;
+        }
     }
     double total = 0.0;
     for (int i = 0; i < n; ++i) {
