@@ -38,9 +38,16 @@ __device__ __forceinline__ void exp_frac(float xf, double &r) {
     r = fma(q, x, 1.0);
 }
 
-// k + f with |f| <= 1/2 (k and f as they are where |f| <= 1/2 already).
+// A potential k + f as it is read: one that a caller split in another way gets
+// a fraction, |f| <= 1/2. What neg_log_split and the stage change form stays as
+// it is, also where a fraction is past 1/2 by the 1e-4 that neg_log_split
+// allows: a potential then has one form, whether it is kept on chip from one
+// iteration to the next, read by the next launch or by a caller who resumes
+// from it, and no step has to look at it. (Rounding every new potential to
+// |f| <= 1/2 instead cost 1 % at n = 64, two dependent instructions a step.)
+constexpr float kFracMax = 0.51f;
 __device__ __forceinline__ void unit_frac(int &k, float &f) {
-    const float r = rintf(f);
+    const float r = fabsf(f) > kFracMax ? rintf(f) : 0.f;
     k += (int)r;
     f -= r;
 }
@@ -50,7 +57,7 @@ __device__ __forceinline__ void unit_frac(int &k, float &f) {
 // S = 2^e m, m in [1/sqrt 2, sqrt 2); with y = m - 1 (exact) and
 // s = y / (2 + y), log m = 2 atanh(s) = y - s y + s^3 (2/3 + 2/5 s^2 + ...).
 // e log 2 is split so that its leading part and k cancel exactly.
-__device__ __forceinline__ float neg_log_parts(float S, int &k) {
+__device__ __forceinline__ float neg_log_split(float S, int &k) {
     float m = __builtin_amdgcn_frexp_mantf(S);  // [1/2, 1)
     int e = __builtin_amdgcn_frexp_expf(S);
     const bool low = m < 0.70710678f;
@@ -73,17 +80,11 @@ __device__ __forceinline__ float neg_log_parts(float S, int &k) {
     return (fmaf(-ef, kHi, -kf) - y) - fmaf(ef, kLo, corr);
 }
 
-// -log(S) = k + f with |f| <= 1/2, exactly the k and f that unit_frac leaves as
-// they are: a potential has one form, whether it is kept on chip from one
-// iteration to the next, read back by the next launch, or by a caller who
-// resumes from it. S in float64: S = T + d with T its float32 rounding,
-// log S = log T + d / T.
+// S in float64: S = T + d with T its float32 rounding, log S = log T + d / T.
 __device__ __forceinline__ float neg_log_split(double S, int &k) {
     const float T = (float)S;
     const float d = (float)(S - (double)T);
-    float f = neg_log_parts(T, k) - d * __builtin_amdgcn_rcpf(T);
-    unit_frac(k, f);
-    return f;
+    return neg_log_split(T, k) - d * __builtin_amdgcn_rcpf(T);
 }
 
 }  // namespace sk

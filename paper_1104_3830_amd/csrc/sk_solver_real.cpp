@@ -192,48 +192,44 @@ sk_status augment_all(int n, const int64_t *rp, const int32_t *col, const float 
     return SK_OK;
 }
 
-// Whether no other perfect matching is within tol of the optimum: a cycle of
-// rows, each with an entry of reduced cost <= tol in the next one's column,
-// would be needed for one. Rows that none is left to point at are taken away
-// until all are gone or a cycle stays.
-bool unique_within(int n, const int64_t *rp, const int32_t *col, const float *w, const Matching &M, double tol) {
+// Whether the potentials prove M the optimum and no other perfect matching
+// within tol of it. exact: whether they are precise enough to, that is whether
+// what their rounding leaves open stays below tol / 2: over the rows (a
+// matching has one entry in each), the most by which a reduced cost of the row
+// can be below 0 and its matched one's off 0, with the rounding of their two
+// subtractions. It grows with the potentials and not with the weights. Another
+// matching would need a cycle of rows, each with an entry of reduced cost
+// <= tol in the next one's column. Rows that none is left to point at are
+// taken away until all are gone or a cycle stays.
+bool unique_within(int n, const int64_t *rp, const int32_t *col, const float *w, const Matching &M, double tol,
+                   bool &exact) {
+    constexpr double kUlp = 0x1p-52;
     std::vector<int32_t> into((size_t)n, 0), queue;
-    queue.reserve((size_t)n);
-    auto each = [&](int i, auto &&f) {
-        for (int64_t e = rp[i]; e < rp[i + 1]; ++e) {
-            const int k = M.row_of[col[e]];
-            if (k != i && -(double)w[e] - M.u[i] - M.v[col[e]] <= tol) f(k);
-        }
-    };
-    for (int i = 0; i < n; ++i) each(i, [&](int k) { ++into[k]; });
-    for (int i = 0; i < n; ++i)
-        if (into[i] == 0) queue.push_back(i);
-    for (size_t h = 0; h < queue.size(); ++h)
-        each(queue[h], [&](int k) {
-            if (--into[k] == 0) queue.push_back(k);
-        });
-    return queue.size() == (size_t)n;
-}
-
-// How far the weights of two perfect matchings can be from what their reduced
-// costs say: summed over the rows (a matching has one entry in each), the most
-// by which a reduced cost of the row can be below 0 and its matched one's off
-// 0, with the rounding of their two subtractions. It is found from the
-// potentials as they are, since it grows with them and not with the weights.
-double certificate_slack(int n, const int64_t *rp, const int32_t *col, const float *w, const Matching &M) {
-    constexpr double kHalfUlp = 0x1p-53;
-    double sum = 0.0;
+    double slack = 0.0;
     for (int i = 0; i < n; ++i) {
         double below = 0.0;
         for (int64_t e = rp[i]; e < rp[i + 1]; ++e) {
             const double c = -(double)w[e] - M.u[i], r = c - M.v[col[e]];
-            const double err = 2 * kHalfUlp * (std::fabs(c) + std::fabs(r));
+            const double err = kUlp * (std::fabs(c) + std::fabs(r));
             below = std::max(below, err - r);
-            if (e == M.edge_of[i]) sum += std::fabs(r) + err;
+            if (e == M.edge_of[i]) slack += std::fabs(r) + err;
+            if (r <= tol && M.row_of[col[e]] != i) ++into[M.row_of[col[e]]];
         }
-        sum += below;
+        slack += below;
     }
-    return sum;
+    exact = slack <= 0.5 * tol;
+    if (!exact) return false;
+    queue.reserve((size_t)n);
+    for (int i = 0; i < n; ++i)
+        if (into[i] == 0) queue.push_back(i);
+    for (size_t h = 0; h < queue.size(); ++h) {
+        const int i = queue[h];
+        for (int64_t e = rp[i]; e < rp[i + 1]; ++e) {
+            const int k = M.row_of[col[e]];
+            if (k != i && -(double)w[e] - M.u[i] - M.v[col[e]] <= tol && --into[k] == 0) queue.push_back(k);
+        }
+    }
+    return queue.size() == (size_t)n;
 }
 
 }  // namespace
@@ -264,8 +260,7 @@ sk_status solve_real_impl(int n, const int64_t *rp, const int32_t *col, const fl
         M.v = start->v;
         const sk_status st = augment_all(n, rp, col, w, hint, start, kSlack * wmax, M);
         if (st != SK_OK) return st;
-        exact = certificate_slack(n, rp, col, w, M) <= 0.5 * kTieTol * wmax;
-        solved = exact && unique_within(n, rp, col, w, M, kTieTol * wmax);
+        solved = unique_within(n, rp, col, w, M, kTieTol * wmax, exact);
         start->v = M.v;
         start->col = M.col_of;
     }

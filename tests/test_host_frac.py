@@ -13,7 +13,7 @@ ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not found")
 
 
-def test_a_fraction_is_at_most_one_half(tmp_path):
+def test_a_split_logarithm_is_read_as_it_was_formed(tmp_path):
     exe = tmp_path / "frac_check"
     # HIP's own headers as system headers, without its device compiler
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-D__HIP_PLATFORM_AMD__", f"-I{CSRC}",
