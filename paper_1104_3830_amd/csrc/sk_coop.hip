@@ -47,18 +47,19 @@ struct CoopInt {
     }
     __device__ __forceinline__ void begin(const Inst &, int p) { p4 = 4 * p; }
 
-    // rows past the matrix (w, F as they come): every exponent 4 G_j + kPadExp4
-    // clamps to the table's zero entry
+    // rows past the matrix: every exponent 4 (p w + G_j) + kPadExp4 clamps to
+    // the table's zero entry (in padding columns the sum may wrap, and what
+    // these add to each other is not used)
     __device__ __forceinline__ void row_terms(const Lds &L, int k, int t, bool on, int F, const int (&A)[8 * CH],
                                               float *e) {
-        const int B = on ? 4 * (F - kTabLo) : kPadExp4, pk = on ? p4 : 0;
+        const int B = on ? 4 * (F - kTabLo) : kPadExp4;
 #pragma unroll
         for (int q = 0; q < CH; ++q) {
             int w[8];
             unpack8i(L.w[k * CH + q][t], w);
 #pragma unroll
             for (int c = 0; c < 8; ++c) {
-                float x = tab_at(L.tab, tab_off(pk, w[c], A[8 * q + c], B));
+                float x = tab_at(L.tab, tab_off(p4, w[c], A[8 * q + c], B));
                 if (SENT) x = w[c] == SK_SENTINEL ? 0.f : x;
                 e[8 * q + c] = x;
             }

@@ -56,9 +56,10 @@ __device__ __forceinline__ float tab_at(const float *tab, int off) {
     return *reinterpret_cast<const float *>(reinterpret_cast<const char *>(tab) + off);
 }
 
-// Byte offset of exp(E) with 4 E - 4 kTabLo = 4 p w + A + B (A, B prescaled).
+// Byte offset of exp(E) with 4 E - 4 kTabLo = 4 p w + A + B (A, B prescaled);
+// a sum outside int32 wraps.
 __device__ __forceinline__ int tab_off(int p4, int w, int A, int B) {
-    const int t = __mul24(p4, w) + A + B;
+    const int t = (int)((unsigned)__mul24(p4, w) + (unsigned)A + (unsigned)B);
     return min(max(t, 0), kTabMaxOff);
 }
 

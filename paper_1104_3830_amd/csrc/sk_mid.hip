@@ -419,18 +419,18 @@ __device__ __forceinline__ void mid_run(const Inst &I, MidLds<CH, FOLD> &L, MidC
                 g[8 * q + c] = on ? k.g : 0.f;
             }
         }
-        // rows past the matrix (w, F as they come): every exponent
-        // 4 G_j + kPadExp4 clamps to the table's zero entry
+        // rows past the matrix: every exponent 4 (p w + G_j) + kPadExp4 clamps
+        // to the table's zero entry (in padding columns the sum may wrap, and
+        // what these add to each other is not used)
         const int Boff = row_on ? 4 * (F - kTabLo) : kPadExp4;
         auto row_terms = [&](int k, int B) {
-            const int pk = rw + k < n ? p4 : 0;
 #pragma unroll
             for (int q = 0; q < CH; ++q) {
                 int w[8];
                 unpack8i(wv[k * CH + q], w);
 #pragma unroll
                 for (int c = 0; c < 8; ++c) {
-                    float x = tab_at(L.tab, tab_off(pk, w[c], A[8 * q + c], B));
+                    float x = tab_at(L.tab, tab_off(p4, w[c], A[8 * q + c], B));
                     if (SENT) x = w[c] == SK_SENTINEL ? 0.f : x;
                     e[k * C + 8 * q + c] = x;
                 }
