@@ -338,7 +338,8 @@ size_t sk_solve_arena_bytes(int32_t n, int32_t storage, int64_t max_kept);
  * arena, sweeps all admitted instances together, and on convergence prunes,
  * solves the reduced instance and checks the certificate. *ticket receives
  * an id for sk_poll. The caller's buffer may be reused when the call
- * returns. Returns SK_EAGAIN when the queue is full or no staging memory is
+ * returns. params->fused is ignored: the instances are swept in two passes.
+ * Returns SK_EAGAIN when the queue is full or no staging memory is
  * free (a pinned ring of 512 MiB; poll finished requests, then submit again). */
 sk_status sk_submit(sk_ctx *ctx, const int16_t *W_host, int32_t n, const sk_params *params,
                     uint64_t *ticket);

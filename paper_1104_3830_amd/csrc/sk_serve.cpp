@@ -574,6 +574,7 @@ extern "C" sk_status sk_submit(sk_ctx *ctx, const int16_t *W_host, int32_t n, co
     Request *r = new Request();
     r->n = n;
     r->prm = *params;
+    r->prm.fused = 0;  // the batch is swept in two passes: the region has no slots for one
     r->len = len;
     r->mid_ok = mid_ok;
     r->t_submit = std::chrono::steady_clock::now();
