@@ -672,7 +672,7 @@ __global__ __launch_bounds__(kFinThreads) void k_col_finalize(const Inst *__rest
     }
     __syncthreads();
     if ((arrived & 0xffffu) != groups - 1u) return;
-    if (conv || capped || arrived > 0xffffu || err || I.deform_a > 0.0) {
+    if (conv || capped || arrived > 0xffffu || err) {
         __threadfence();
         iteration_end(I, ctl, res, conv, L);
         return;
@@ -686,6 +686,9 @@ __global__ __launch_bounds__(kFinThreads) void k_col_finalize(const Inst *__rest
         atomicAdd((unsigned long long *)&ctl->iters_total, 1ull);
         atomicAdd((unsigned long long *)&ctl->stage_iters[stage], 1ull);
     }
+    // deformed iteration: the next one's p (a logarithm each)
+    if (I.deform_a > 0.0 && t == 0) ctl->p = deform_p(I, iter + 2);
+    if (I.deform_a > 0.0 && t == kWave) ctl->preal = deform_p_real(I, iter + 2);
 }
 
 // ---------------------------------------------------------------- FP64 recheck

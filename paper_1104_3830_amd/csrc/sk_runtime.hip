@@ -887,7 +887,7 @@ sk_status sk::run_batch_i16(sk_ctx *ctx, Batch &B, const sk_params *prm, int fir
     // instance paused at each stage end the first block is the previous
     // stage's length, the next ones kTailBlock.
     constexpr int kTailBlock = 8;
-    int blk = std::min(check, 2 * std::max(1, prm->n_p - first_stage));
+    int blk = prm->deform_a > 0.0 ? check : std::min(check, 2 * std::max(1, prm->n_p - first_stage));
     auto left = [&](const Inst &I, const Ctl &c) -> int64_t {
         if (I.deform_a > 0.0) return check;  // one long stage
         if (I.pause || c.stage == 0) return kTailBlock;
