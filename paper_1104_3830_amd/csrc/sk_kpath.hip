@@ -647,7 +647,10 @@ sk_status run_single_k(sk_ctx *ctx, Batch &B, const sk_params *prm, const StageH
         if (++rounds > bound) return fail(ctx, SK_EDEVICE, "stored-K controller did not terminate");
         if (c.state == ST_ERROR || c.state == ST_DONE) break;
         if (c.state == ST_STAGE_END) {
-            if (c.stage + 1 >= prm->n_p) {
+            // a stage whose one iteration was the log-domain one before K is
+            // formed (max_iters_per_stage = 1) has no K and no scalings to fold
+            const bool formed = !c.need_absorb;
+            if (formed && c.stage + 1 >= prm->n_p) {
                 // FP64 sums of the balanced matrix K a b, before folding
                 const Inst &I = B.h_insts[0];
                 const int n = I.n;
@@ -670,7 +673,7 @@ sk_status run_single_k(sk_ctx *ctx, Batch &B, const sk_params *prm, const StageH
                 ctx->k_res_rows = rr;
                 ctx->k_res_cols = cr;
             }
-            if ((st = fold(ctx, B)) != SK_OK) return st;
+            if (formed && (st = fold(ctx, B)) != SK_OK) return st;
             if (hook) {
                 bool stop = false;
                 if ((st = (*hook)(stop)) != SK_OK) return st;

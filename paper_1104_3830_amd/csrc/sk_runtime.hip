@@ -1144,7 +1144,7 @@ sk_status sk::scale_impl(sk_ctx *ctx, int count, const int16_t *const *W, const 
         rep.absorbs = ctx->absorbs;
         if (!(c.err & (ERR_EMPTY_ROW | ERR_EMPTY_COL))) {
             report_from_check(ctx->h_checkout + 4 * (size_t)k, c.p, &rep);
-            if (prm->storage != SK_W_I16) {
+            if (prm->storage != SK_W_I16 && !std::isnan(ctx->k_res_rows)) {
                 rep.residual_fp64 = ctx->k_res_rows;
                 rep.col_residual_fp64 = ctx->k_res_cols;
             }
