@@ -114,7 +114,8 @@ static const int kServeSmallIters = 64;
 static const size_t kTablesBytes = size_t(64) << 20;
 
 // Host copy of a submitted W into staging: one thread per kCopyChunk bytes,
-// at most kCopyThreads (a single thread copies at about 25-30 GB/s).
+// at most kCopyThreads (into pinned memory 32 GB/s with one thread, 60 with
+// two, 88 with four, for 128 MB).
 static const size_t kCopyChunk = size_t(8) << 20;
 static const int kCopyThreads = 4;
 
