@@ -130,12 +130,17 @@ def parse():
     return ap.parse_args()
 
 
+def _base_name(name):
+    """A kernel's name with its template arguments, without its parameters."""
+    return name.replace("(anonymous namespace)::", "").split("(")[0]
+
+
 def trace_summary(path):
     import csv
     per = {}
     for r in csv.DictReader(open(path)):
         d = int(r["End_Timestamp"]) - int(r["Start_Timestamp"])
-        per.setdefault(r["Kernel_Name"].split("(")[0], []).append(d)
+        per.setdefault(_base_name(r["Kernel_Name"]), []).append(d)
     for k, v in sorted(per.items(), key=lambda kv: -sum(kv[1])):
         big = [x for x in v if x > 20000]
         print(f"{k} calls={len(v)} avg_ns={sum(v) / len(v):.0f} calls_over_20us={len(big)} "
@@ -150,7 +155,7 @@ def counter_summary(path):
     import csv
     per = {}
     for r in csv.DictReader(open(path)):
-        k = r["Kernel_Name"].split("(")[0]
+        k = _base_name(r["Kernel_Name"])
         d = per.setdefault(k, {}).setdefault(r["Dispatch_Id"], {})
         d[r["Counter_Name"]] = d.get(r["Counter_Name"], 0.0) + float(r["Counter_Value"])
     for k, disp in sorted(per.items()):
@@ -178,7 +183,7 @@ def source_hash():
 def _kernel_key(name):
     """'void sk::k_row_sweep<true>(...)' -> 'sk::k_row_sweep'."""
     import re
-    k = name.split("(")[0]
+    k = _base_name(name)
     k = re.sub(r"<[^<>]*>$", "", k)
     return k[5:] if k.startswith("void ") else k
 
@@ -233,7 +238,7 @@ def _counter_means_full(path, counter):
     for r in csv.DictReader(open(path)):
         if r["Counter_Name"] != counter:
             continue
-        k = r["Kernel_Name"].split("(")[0]
+        k = _base_name(r["Kernel_Name"])
         k = k[5:] if k.startswith("void ") else k
         per.setdefault(k, {}).setdefault(r["Dispatch_Id"], 0.0)
         per[k][r["Dispatch_Id"]] += float(r["Counter_Value"])
