@@ -62,6 +62,7 @@ sk_status plan_real(sk_ctx *ctx, Bump &bump, const float *W, int32_t n, const sk
         return fail(ctx, SK_EINVAL, "p * (w_max - w_min) = %g exceeds 1e8", (double)pmax * pscale * range);
     const int64_t pitch = n;
     const int16_t *Ws[1] = {nullptr};
+    const std::string err = ctx->err;
     for (int lean = 0; lean < 2; ++lean) {
         Bump b = bump;
         B.h_insts.assign(1, Inst{});
@@ -70,6 +71,7 @@ sk_status plan_real(sk_ctx *ctx, Bump &bump, const float *W, int32_t n, const sk
         B.h_insts[0].wref = hi;
         B.h_insts[0].pscale = pscale;
         if ((st = finish_tables(ctx, b, B, lean != 0, solve)) == SK_OK) {
+            ctx->err = err;
             bump = b;
             take_resident(bump, B);
         }

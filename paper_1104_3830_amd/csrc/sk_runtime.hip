@@ -655,7 +655,7 @@ sk_status sk::finish_tables(sk_ctx *ctx, Bump &bump, Batch &B, bool lean, bool s
         if (!B.d_rp || !B.d_hint) return fail(ctx, SK_ENOMEM, "arena too small for the reduced matrix (row pointers)");
     }
     B.scratch_at = align_up(bump.off, 256);
-    if (!B.h_insts[0].colpart && !carve_scratch(bump, B.h_insts[0]))
+    if (B.count == 1 && !B.h_insts[0].colpart && !carve_scratch(bump, B.h_insts[0]))
         return fail(ctx, SK_ENOMEM, "arena too small for the column partials");
     // the check's scratch: consecutive instances share it group by group
     size_t chk_cap = lean ? chk_max : check_scratch(chk_max, chk_sum);
@@ -728,6 +728,7 @@ sk_status sk::plan_batch(sk_ctx *ctx, Bump &bump, int count, const int16_t *cons
     // batch tables the least. Newton's vectors follow the plan, which
     // leaves them as much as there can be.
     const bool one = count == 1, newton = prm->method == SK_NEWTON;
+    const std::string err = ctx->err;  // a plan that did not fit is no error of the call
     sk_status st = SK_ENOMEM;
     for (int lean = newton ? 1 : 0; lean < 2; ++lean) {
         Bump b = bump;
@@ -737,6 +738,7 @@ sk_status sk::plan_batch(sk_ctx *ctx, Bump &bump, int count, const int16_t *cons
         st = k < count ? fail(ctx, SK_ENOMEM, "arena too small for instance %d (n=%d)", k, n[k])
                        : finish_tables(ctx, b, B, lean != 0, solve);
         if (st == SK_OK) {
+            ctx->err = err;
             bump = b;
             take_resident(bump, B);
             if (newton) B.scratch_at = 0;

@@ -240,12 +240,14 @@ static sk_status rebuild(Server *S) {
     S->d_init_units = tb.take<RowUnit>(kLdsMaxN / kRowWaves * 64);
     S->d_fresh = tb.take<int>(kMaxBatch);
     const Bump start = tb;
+    const std::string err = ctx->err;
     sk_status st = finish_tables(ctx, tb, S->B);
     if (st == SK_ENOMEM) {
         tb = start;
         st = finish_tables(ctx, tb, S->B, true);
     }
     if (st != SK_OK) return st;
+    ctx->err = err;
     return upload_batch(ctx, S->B);
 }
 

@@ -72,6 +72,15 @@ def test_real(n, nbytes):
     same(tight, roomy, n, bits=False)
 
 
+def test_a_smaller_plan_is_no_error():
+    ctx = TightContext(0, arena_bytes=154112)
+    prm = sk.make_params([1], tol=1e-1, max_iters=400)
+    ctx.scale(uniform(1024, 1), prm)
+    assert ctx.last_error() == ""
+    ctx.scale_real(torch.from_numpy(skgen.euclidean_real(1024, seed=1)).cuda(), prm)
+    assert ctx.last_error() == ""
+
+
 def test_served():
     """A served request whose region only has the sweeps' room."""
     n = 1024
