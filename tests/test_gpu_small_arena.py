@@ -72,6 +72,25 @@ def test_real(n, nbytes):
     same(tight, roomy, n, bits=False)
 
 
+@pytest.mark.parametrize("ns", [[1000], [300, 1000, 64], [777] * 40, [1001, 2000]])
+def test_the_stated_size_holds_the_fastest_plan(ns):
+    """In an arena of exactly the size that the sizing functions give, the bits
+    are those of a roomy one."""
+    import ctypes
+    Ws = [uniform(n, k) for k, n in enumerate(ns)]
+    prm = sk.make_params([1, 2], tol=0.0, max_iters=4)
+    size = sk.lib().sk_batch_arena_bytes(len(ns), (ctypes.c_int32 * len(ns))(*ns), 0)
+    ctx, roomy = TightContext(0, arena_bytes=size), sk.Context(0, arena_bytes=256 << 20)
+    for a, b, n in zip(ctx.scale_batch(Ws, prm), roomy.scale_batch(Ws, prm), ns):
+        same(a, b, n, bits=True)
+    assert ctx.guard_untouched()
+    if len(ns) == 1:
+        X = torch.from_numpy(skgen.euclidean_real(ns[0], seed=1)).cuda()
+        ctx = TightContext(0, arena_bytes=sk.lib().sk_real_arena_bytes(ns[0], 0))
+        same(ctx.scale_real(X, prm), roomy.scale_real(X, prm), ns[0], bits=True)
+        assert ctx.guard_untouched()
+
+
 def test_a_smaller_plan_is_no_error():
     ctx = TightContext(0, arena_bytes=154112)
     prm = sk.make_params([1], tol=1e-1, max_iters=400)
